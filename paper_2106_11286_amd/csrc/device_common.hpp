@@ -177,26 +177,72 @@ __device__ __forceinline__ uint32_t xcd_id()
     return v & 7u;
 }
 
+// Exchange of two doubles between lane halves (HALF = 32: upper half of a with
+// lower half of b; HALF = 16: odd rows of a with even rows of b), and the sum
+// of the exchanged pair: each half (row) then holds one of the two operands,
+// added over both halves (rows).
+template <int HALF> __device__ __forceinline__ double swap_sum(double a, double b)
+{
+    typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+    v2u lo, hi;
+    if constexpr (HALF == 32) {
+        lo = __builtin_amdgcn_permlane32_swap((uint32_t)__double2loint(a), (uint32_t)__double2loint(b), false, false);
+        hi = __builtin_amdgcn_permlane32_swap((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b), false, false);
+    } else {
+        lo = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(a), (uint32_t)__double2loint(b), false, false);
+        hi = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b), false, false);
+    }
+    const uint32_t l0 = lo.x, l1 = lo.y, h0 = hi.x, h1 = hi.y;
+    return __hiloint2double((int)h0, (int)l0) + __hiloint2double((int)h1, (int)l1);
+}
+template <int CTRL> __device__ __forceinline__ double dpp_add(double v)
+{
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return v + __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                                __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+}
+
+// Sums of Q_N doubles over a wave, in a fixed order: lane 8 j + i returns the
+// sum of quantity wave_sum_slot(j).  Every step halves the number of values a
+// lane carries (two quantities share a register after each exchange), so the
+// six sums take 10 additions and no LDS traffic; butterflies of each quantity
+// took 36 additions and 72 lane permutes through the LDS.
+__device__ __forceinline__ double wave_sums(const double (&a)[Q_N])
+{
+    static_assert(Q_N == 6, "the exchange pattern is for six quantities");
+    const double b0 = swap_sum<32>(a[0], a[1]); // halves: 0 | 1
+    const double b1 = swap_sum<32>(a[2], a[3]); // 2 | 3
+    const double b2 = swap_sum<32>(a[4], a[5]); // 4 | 5
+    const double c0 = swap_sum<16>(b0, b1);     // rows: 0 2 1 3
+    const double c1 = swap_sum<16>(b2, b2);     // rows: 4 4 5 5
+    const double d0 = dpp_add<0x128>(c0), d1 = dpp_add<0x128>(c1); // row_ror:8
+    double v = (threadIdx.x & 8u) ? d1 : d0; // eighths: 0 4 2 4 1 5 3 5
+    v = dpp_add<0x141>(v);                   // row_half_mirror
+    v = dpp_add<0xB1>(v);                    // quad_perm [1,0,3,2]
+    return dpp_add<0x4E>(v);                 // quad_perm [2,3,0,1]
+}
+// Quantity that the lanes of eighth j of a wave hold, -1 for a repeated one.
+__device__ __forceinline__ int wave_sum_slot(int j)
+{
+    return j == 0 ? 0 : j == 1 ? 4 : j == 2 ? 2 : j == 4 ? 1 : j == 5 ? 5 : j == 6 ? 3 : -1;
+}
+// The wave's sums, one lane per quantity, into dst[0 .. Q_N).
+template <typename P> __device__ __forceinline__ void store_wave_sums(const double (&a)[Q_N], P dst)
+{
+    const double v = wave_sums(a);
+    const int lane = threadIdx.x & 63, q = wave_sum_slot(lane >> 3);
+    if ((lane & 7) == 0 && q >= 0) dst[q] = v;
+}
+
 // ---------------------------------------------------------------------------
-// Block reduction of Q_N doubles (fixed order: wave butterflies, then waves in
-// index order), written to one partial slot.
+// Block reduction of Q_N doubles (fixed order: wave sums, then waves in index
+// order), written to one partial slot.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void block_store_partials(double (&a)[Q_N], double *dst)
 {
     __shared__ double red[16][Q_N]; // up to 1024 threads
-#pragma unroll
-    for (int q = 0; q < Q_N; ++q) {
-        double v = a[q];
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-        a[q] = v;
-    }
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int n_waves = (blockDim.x + 63) >> 6;
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < Q_N; ++q) red[wave][q] = a[q];
-    }
+    store_wave_sums(a, red[threadIdx.x >> 6]);
     __syncthreads();
     if (threadIdx.x < Q_N) {
         double s = 0.0;

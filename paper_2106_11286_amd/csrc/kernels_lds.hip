@@ -37,19 +37,8 @@ __device__ __forceinline__ uint32_t div_of(uint32_t n, FastDiv f)
 __device__ __forceinline__ void block_reduce_1024(double (&a)[Q_N], double *out)
 {
     __shared__ double red[16][Q_N];
-#pragma unroll
-    for (int q = 0; q < Q_N; ++q) {
-        double v = a[q];
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-        a[q] = v;
-    }
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int n_waves = (blockDim.x + 63) >> 6;
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < Q_N; ++q) red[wave][q] = a[q];
-    }
+    store_wave_sums(a, red[threadIdx.x >> 6]);
     __syncthreads();
     if (threadIdx.x < Q_N) {
         double v = 0.0;
