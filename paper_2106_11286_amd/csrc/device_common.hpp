@@ -335,31 +335,46 @@ __device__ __forceinline__ void sc_site_field(P gx, P gy, P gz, uint32_t oth, in
                                               int Lz, bool px, bool py, bool pz, int xh, int y,
                                               int z, int p, T &hx, T &hy, T &hz)
 {
-    const int ym = y > 0 ? y - 1 : (py ? Ly - 1 : -1);
-    const int yp = y < Ly - 1 ? y + 1 : (py ? 0 : -1);
-    const int xm = xh > 0 ? xh - 1 : (px ? Lxh - 1 : -1);
-    const int xp = xh < Lxh - 1 ? xh + 1 : (px ? 0 : -1);
-    const int zm = z > 0 ? z - 1 : (pz ? Lz - 1 : -1);
-    const int zp = z < Lz - 1 ? z + 1 : (pz ? 0 : -1);
-    hx = 0;
-    hy = 0;
-    hz = 0;
-    auto add = [&](int valid, uint32_t j) {
-        if (valid) {
-            hx += gx[oth + j];
-            hy += gy[oth + j];
-            hz += gz[oth + j];
-        }
-    };
-    add(zm >= 0, (uint32_t)(zm * Ly + y) * Lxh + xh);
-    add(ym >= 0, (uint32_t)(z * Ly + ym) * Lxh + xh);
+    // Every load is issued before the first addition, at the wrapped position
+    // in any case; across an open face (a uniform branch that periodic
+    // lattices skip) it then counts as zero, which changes nothing: the sums
+    // start at +0 and cannot become -0.
+    const int ym = y > 0 ? y - 1 : Ly - 1, yp = y < Ly - 1 ? y + 1 : 0;
+    const int xm = xh > 0 ? xh - 1 : Lxh - 1, xp = xh < Lxh - 1 ? xh + 1 : 0;
+    const int zm = z > 0 ? z - 1 : Lz - 1, zp = z < Lz - 1 ? z + 1 : 0;
     const int xl = p ? xh : xm; // x-1
     const int xr = p ? xp : xh; // x+1
     const uint32_t row = (uint32_t)(z * Ly + y) * Lxh;
-    add(xl >= 0, row + xl);
-    add(xr >= 0, row + xr);
-    add(yp >= 0, (uint32_t)(z * Ly + yp) * Lxh + xh);
-    add(zp >= 0, (uint32_t)(zp * Ly + y) * Lxh + xh);
+    const uint32_t at[6] = {(uint32_t)(zm * Ly + y) * Lxh + xh, (uint32_t)(z * Ly + ym) * Lxh + xh,
+                            row + xl,                           row + xr,
+                            (uint32_t)(z * Ly + yp) * Lxh + xh, (uint32_t)(zp * Ly + y) * Lxh + xh};
+    T vx[6], vy[6], vz[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        vx[k] = gx[oth + at[k]];
+        vy[k] = gy[oth + at[k]];
+        vz[k] = gz[oth + at[k]];
+    }
+    if (!(px && py && pz)) {
+        const bool ok[6] = {pz || z > 0,
+                            py || y > 0,
+                            px || p || xh > 0,
+                            px || !p || xh < Lxh - 1,
+                            py || y < Ly - 1,
+                            pz || z < Lz - 1};
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+            if (!ok[k]) vx[k] = vy[k] = vz[k] = T(0);
+    }
+    hx = 0;
+    hy = 0;
+    hz = 0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        hx += vx[k];
+        hy += vy[k];
+        hz += vz[k];
+    }
 }
 
 template <typename T> struct Vec3 {
