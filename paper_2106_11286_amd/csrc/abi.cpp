@@ -496,8 +496,9 @@ mc_status enqueue_lds(mc_sim *h, uint32_t n, bool measure, uint32_t slot0)
 
 // Enqueue n sweeps (passes, optional finalise into ring slots slot0.., then
 // the counter advance).  Pure launches: safe inside stream capture.
-mc_status enqueue_sweeps(mc_sim *h, uint32_t n, bool measure, uint32_t slot0)
+mc_status enqueue_sweeps(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool to_host = false)
 {
+    if (h->team_on) return enqueue_team(h, n, measure, slot0, to_host);
     if (h->tile.kernel == KERNEL_LDS) return enqueue_lds(h, n, measure, slot0);
     const bool f64 = h->prec == MC_F64;
     const uint32_t n_items = (uint32_t)h->work.size();
@@ -617,7 +618,9 @@ bool persistent_supported(const Tile &t)
 // the counter advance).  Pure launches: safe inside stream capture.
 mc_status enqueue_persistent(mc_sim *h, uint32_t n, bool measure, uint32_t slot0)
 {
-    if (h->tile.kernel == KERNEL_LDS) return enqueue_lds(h, n, measure, slot0);
+    if (h->tile.kernel == KERNEL_LDS)
+        return h->team_on ? enqueue_team(h, n, measure, slot0, false)
+                          : enqueue_lds(h, n, measure, slot0);
     if (!persistent_supported(h->tile))
         return fail(MC_E_UNSUPPORTED, "persistent sweeps: no kernel for this tile (%d rows "
                                       "per thread); use strips of 2 or 4 rows, pairs of 1 or "
@@ -649,10 +652,15 @@ mc_status enqueue_persistent(mc_sim *h, uint32_t n, bool measure, uint32_t slot0
     return MC_OK;
 }
 
-// After a synchronisation: report a persistent launch whose bounded wait gave
-// up (the spins of that call are then incomplete).
+// After a synchronisation: report a team or persistent launch whose bounded
+// wait gave up (the spins of that call are then incomplete).
 mc_status check_persistent(mc_sim *h)
 {
+    if (*h->host_flag) {
+        *h->host_flag = 0;
+        return fail(MC_E_DEVICE, "team sweep: a wait for a neighbouring workgroup's planes gave "
+                                 "up; the state of that call is incomplete");
+    }
     if (!h->persist_used) return MC_OK;
     uint32_t hdr[2] = {0, 0};
     HIP_TRY(hipMemcpy(hdr, h->pstate, sizeof hdr, hipMemcpyDeviceToHost));
@@ -979,12 +987,16 @@ mc_status mc_init_lattice(const mc_replica_desc *reps, int32_t n_reps, mc_precis
         h->n_occ[r] = count_occupied(d);
         if (h->n_occ[r] == 0) return cleanup(fail(MC_E_ARG, "replica %d has no occupied site", r));
     }
-    if (hipHostMalloc((void **)&h->host_rec, sizeof(double) * NR * n_reps * (kRing + 1),
+    // the ring with its measurement slot, the last sweep's records, a flag word
+    if (hipHostMalloc((void **)&h->host_rec, sizeof(double) * NR * (n_reps * (kRing + 2ull) + 1),
                       hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         h->host_rec = nullptr;
         return cleanup(fail(MC_E_DEVICE, "pinned host allocation failed"));
     }
+    h->host_last = h->host_rec + (size_t)NR * n_reps * (kRing + 1);
+    h->host_flag = (volatile uint32_t *)(h->host_last + (size_t)NR * n_reps);
+    *h->host_flag = 0;
     h->xcd_ok = device_deals_xcds(h, h->queues_dev);
     mc_status s;
     if ((s = plan_queues(h)) != MC_OK) return cleanup(s);
@@ -1035,6 +1047,8 @@ mc_status mc_init_lattice(const mc_replica_desc *reps, int32_t n_reps, mc_precis
             h->tile = Tile{KERNEL_LDS, lds_threads(h), 1, 1};
         (void)hipGetLastError();
     }
+    h->default_tile = h->tile;
+    team_init(h);
     *out = h;
     return MC_OK;
 }
@@ -1051,12 +1065,15 @@ mc_status mc_sweep(mc_sim *h, uint32_t n_sweeps, uint32_t flags)
     if (h->t + n_sweeps > 0xFFFFFFFFull) return fail(MC_E_STATE, "sweep counter would exceed 2^32-1");
     const bool measure = flags & MC_MEASURE;
     const uint32_t slot0 = (uint32_t)(h->n_measured % kRing);
-    mc_status s = (flags & MC_PERSISTENT) ? enqueue_persistent(h, n_sweeps, measure, slot0)
-                                          : enqueue_sweeps(h, n_sweeps, measure, slot0);
+    const bool to_host = h->team_on && !(flags & MC_PERSISTENT);
+    mc_status s = (flags & MC_PERSISTENT)
+                      ? enqueue_persistent(h, n_sweeps, measure, slot0)
+                      : enqueue_sweeps(h, n_sweeps, measure, slot0, to_host);
     if (s != MC_OK) return s;
     note_sweeps(h, n_sweeps);
     h->t += n_sweeps;
     if (measure) {
+        h->last_on_host = to_host;
         h->n_measured += n_sweeps;
         h->last_slot = (int64_t)((slot0 + n_sweeps - 1) % kRing);
     }
@@ -1080,7 +1097,9 @@ mc_status mc_sweep_timed(mc_sim *h, uint32_t n_sweeps, uint32_t flags, double *p
         HIP_TRY(hipEventCreate(&e1));
         const uint32_t slot0 = (uint32_t)(h->n_measured % kRing);
         hipError_t err = hipEventRecord(e0, h->stream);
-        mc_status st = err == hipSuccess ? enqueue_lds(h, n_sweeps, measure, slot0) : MC_OK;
+        mc_status st = err != hipSuccess ? MC_OK
+                       : h->team_on      ? enqueue_team(h, n_sweeps, measure, slot0, false)
+                                         : enqueue_lds(h, n_sweeps, measure, slot0);
         if (err == hipSuccess && st == MC_OK) err = hipEventRecord(e1, h->stream);
         if (err == hipSuccess && st == MC_OK) err = hipEventSynchronize(e1);
         float ms = 0.f;
@@ -1091,6 +1110,7 @@ mc_status mc_sweep_timed(mc_sim *h, uint32_t n_sweeps, uint32_t flags, double *p
         if (err != hipSuccess) return fail(MC_E_DEVICE, "timed sweeps: %s", hipGetErrorString(err));
         h->t += n_sweeps;
         if (measure) {
+            h->last_on_host = false;
             h->n_measured += n_sweeps;
             h->last_slot = (int64_t)((slot0 + n_sweeps - 1) % kRing);
         }
@@ -1150,6 +1170,7 @@ mc_status mc_sweep_timed(mc_sim *h, uint32_t n_sweeps, uint32_t flags, double *p
     note_sweeps(h, n_sweeps);
     h->t += n_sweeps;
     if (measure) {
+        h->last_on_host = false;
         h->n_measured += n_sweeps;
         h->last_slot = (int64_t)((slot0 + n_sweeps - 1) % kRing);
     }
@@ -1165,6 +1186,11 @@ mc_status mc_observables(mc_sim *h, mc_obs *out, int32_t n_reps)
     HIP_TRY(hipStreamSynchronize(h->stream));
     mc_status ps = check_persistent(h);
     if (ps != MC_OK) return ps;
+    if (h->last_on_host) { // the device wrote them to pinned memory
+        for (int r = 0; r < h->n_reps; ++r)
+            record_to_obs(h, h->host_last + (size_t)r * NR, r, &out[r]);
+        return MC_OK;
+    }
     const size_t sz = sizeof(double) * NR * h->n_reps;
     HIP_TRY(hipMemcpyAsync(h->host_rec, h->records + (size_t)h->last_slot * h->n_reps * NR, sz,
                            hipMemcpyDeviceToHost, h->stream));
@@ -1283,6 +1309,7 @@ mc_status mc_run_schedule(mc_sim *h, const mc_schedule *s, mc_obs *series, uint6
             if ((st = run_chunk(h, k, true, 0, persistent)) != MC_OK) return st;
             h->t += k;
             h->n_measured += k;
+            h->last_on_host = false;
             h->last_slot = k - 1;
             const size_t sz = sizeof(double) * NR * h->n_reps * k;
             HIP_TRY(hipMemcpyAsync(h->host_rec, h->records, sz, hipMemcpyDeviceToHost, h->stream));
@@ -1454,6 +1481,7 @@ mc_status mc_set_tile(mc_sim *h, int32_t kernel, int32_t tx, int32_t ty, int32_t
         HIP_TRY(lds_allow(h->kind, h->prec == MC_F64, (uint32_t)lds_need(h)));
         for (auto &kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
         h->graphs.clear();
+        h->team_on = false;
         h->tile = Tile{KERNEL_LDS, tx, 1, 1};
         h->tuned_persistent = false; // a tile set by hand runs per pass under MC_TUNED_LAUNCH
         return MC_OK;
@@ -1535,6 +1563,7 @@ mc_status mc_set_tile(mc_sim *h, int32_t kernel, int32_t tx, int32_t ty, int32_t
     }
     for (auto &kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
     h->graphs.clear();
+    h->team_on = false;
     h->tile = t;
     h->pass_tile = t;
     h->tuned_persistent = false;
@@ -1603,6 +1632,7 @@ void mc_destroy(mc_sim *h)
     if (h->stream || h->scratch) (void)hipStreamSynchronize(h->stream);
     for (auto &kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
     h->graphs.clear();
+    team_release(h);
     if (h->host_rec) (void)hipHostFree(h->host_rec);
     h->magic = 0;
     delete h;

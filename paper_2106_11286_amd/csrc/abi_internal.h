@@ -94,6 +94,20 @@ struct mc_sim {
     uint32_t n_queues = 1, max_queue_items = 0;
     std::vector<uint32_t> q_host;   // queue table as uploaded (offsets [16], items)
     double *host_rec = nullptr; // pinned, (kRing + 1) * n_reps * NR
+    double *host_last = nullptr; // pinned, written by the device: records of the last
+                                 // measured sweep of mc_sweep [n_reps][NR]
+    volatile uint32_t *host_flag = nullptr; // pinned: a team sweep's bounded wait gave up
+    bool last_on_host = false;   // host_last holds the last measured sweep
+    // team sweeps (kernels_team.hip): a workspace of the handle's own
+    Tile default_tile{};         // the tile chosen by mc_init_lattice
+    bool team_on = false;        // sweeps of the default tile run by teams
+    char *team_ws = nullptr;     // device memory, null: no team for these lattices
+    mc::TeamWg *team_wgs = nullptr;
+    uint64_t *team_words = nullptr;
+    double *team_partials = nullptr;
+    uint32_t *team_state = nullptr; // epoch, abort, done[1 + n_reps]
+    uint32_t team_grid = 0, team_lds = 0;
+    int team_threads = 0;
     uint64_t t = 0;             // sweeps done
     uint64_t n_measured = 0;
     int64_t last_slot = -1;
@@ -111,6 +125,12 @@ uint32_t measure_blocks(const RepDev &R);
 mc_status check_measure_args(const mc_replica_desc *d, mc_precision prec,
                              const mc_spin_buffers *bufs, const double *record_dev);
 bool lds_fits(const mc_sim *h);
+// Team sweeps (abi_team.cpp): plan the teams of a new handle and allocate
+// their workspace, where the lattices are small enough to gain from them
+// (leaves team_ws null otherwise); release it; enqueue n sweeps.
+void team_init(mc_sim *h);
+void team_release(mc_sim *h);
+mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool to_host);
 // A simple-cubic handle with a replica cut to a sphere (tile and LDS kernels only).
 bool sc_sphere(const mc_sim *h);
 mc_status check_persistent(mc_sim *h);

@@ -1,0 +1,221 @@
+// abi_team.cpp -- team sweeps of small lattices (kernels_team.hip): which
+// handles use them, how the planes are dealt to workgroups, and their launches.
+#include <algorithm>
+#include <cstdint>
+#include <cstring>
+#include <vector>
+
+#include "abi_internal.h"
+
+using namespace mcabi;
+
+namespace {
+
+// Sweeps per measured launch (a launch keeps the sums of every sweep).
+constexpr uint32_t kTeamChunk = 64;
+// Sweeps per unmeasured launch (bounds one launch to some tens of ms).
+constexpr uint32_t kTeamLong = 4096;
+// Polls of a word before a workgroup gives up (about 0.5 us each).
+constexpr uint32_t kTeamSpins = 1u << 22;
+// Kernels that may hold the GPU beside one another (hardware queues of a
+// process); the workgroups of that many team launches fit the GPU together,
+// so each launch's workgroups all get to run whatever else is queued.
+constexpr uint32_t kTeamShare = 4;
+
+// A colour pass of its own launch takes about 4.4 us on a lattice this small
+// (sc 24^3 .. 64^3: 8.7 to 9.3 us per sweep, 14.5 to 15.4 measured).
+constexpr double kTeamPhaseUs = 4.5;
+// Box sites of a handle: beyond, a pass launch is no longer mostly overhead.
+constexpr uint64_t kTeamSites = 400000;
+
+struct TeamPlan {
+    std::vector<TeamWg> wgs;
+    uint64_t words = 0;
+    uint32_t lds = 0;
+    int threads = 0;
+    double phase_us = 0.0; // expected time of a colour phase
+    bool teams = false;    // some replica has more than one workgroup
+};
+
+// Deal every replica's planes so that a workgroup holds about `q` sites of a colour.
+TeamPlan plan_teams(const mc_sim *h, uint32_t q)
+{
+    TeamPlan P;
+    const int esz = h->prec == MC_F64 ? 8 : 4, nc = h->n_colours, nw = h->prec == MC_F64 ? 6 : 3;
+    uint32_t most = 1, plane_most = 1;
+    for (int r = 0; r < h->n_reps; ++r) {
+        const RepDev &R = h->reps[r];
+        const uint32_t psites = (uint32_t)R.Lxh * (uint32_t)R.Ly;
+        const int nz = (int)std::min<uint32_t>((uint32_t)R.Lz, std::max(1u, q / psites));
+        const int members = (R.Lz + nz - 1) / nz;
+        const bool per = (R.pmask & 4u) != 0;
+        // slots: one per outer plane of a workgroup
+        std::vector<int> lo_slot(members), hi_slot(members);
+        int slots = 0;
+        for (int m = 0; m < members; ++m) {
+            const int n = std::min(nz, R.Lz - m * nz);
+            lo_slot[m] = slots++;
+            hi_slot[m] = n > 1 ? slots++ : lo_slot[m];
+        }
+        const uint32_t first = (uint32_t)P.wgs.size();
+        for (int m = 0; m < members; ++m) {
+            TeamWg w;
+            std::memset(&w, 0, sizeof w);
+            w.rep = (uint32_t)r;
+            w.z0 = m * nz;
+            w.nz = std::min(nz, R.Lz - w.z0);
+            const int below = m > 0 ? m - 1 : (per ? members - 1 : -1);
+            const int above = m < members - 1 ? m + 1 : (per ? 0 : -1);
+            w.z_lo = w.z0 > 0 ? w.z0 - 1 : (per ? R.Lz - 1 : -1);
+            w.z_hi = w.z0 + w.nz < R.Lz ? w.z0 + w.nz : (per ? 0 : -1);
+            const bool team = members > 1;
+            w.lo = team && below >= 0 ? hi_slot[below] : -1;
+            w.hi = team && above >= 0 ? lo_slot[above] : -1;
+            w.own_lo = team && below >= 0 ? lo_slot[m] : -1;
+            w.own_hi = team && above >= 0 ? hi_slot[m] : -1;
+            w.first = first;
+            w.members = (uint32_t)members;
+            w.words = P.words;
+            P.wgs.push_back(w);
+        }
+        P.teams |= members > 1;
+        if (members > 1) P.words += (uint64_t)slots * nc * nw * psites;
+        P.lds = std::max<uint32_t>(
+            P.lds, (uint32_t)std::min<uint64_t>(0xFFFFFFFFu, team_lds_bytes(h->kind, psites, nz, esz)));
+        most = std::max(most, psites * (uint32_t)nz);
+        plane_most = std::max(plane_most, psites);
+    }
+    P.threads = (int)std::min<uint32_t>(TEAM_THREADS, (most + 63u) / 64u * 64u);
+    // microseconds of a colour phase, fitted to sc 16^3 .. 48^3, 17 x 24^3 and
+    // 50 x 37 x 23: the exchange, then rounds of updates and of polled words
+    const uint32_t rounds = (most + (uint32_t)P.threads - 1) / (uint32_t)P.threads;
+    const uint32_t polls = (plane_most + (uint32_t)P.threads - 1) / (uint32_t)P.threads;
+    P.phase_us = 1.0 + (h->prec == MC_F64 ? 1.5 : 0.65) * rounds +
+                 (h->prec == MC_F64 ? 0.8 : 0.55) * polls;
+    return P;
+}
+
+} // namespace
+
+namespace mcabi {
+
+void team_init(mc_sim *h)
+{
+    h->team_ws = nullptr;
+    h->team_on = false;
+    // The LDS kernel (one workgroup per replica) is the faster one while a
+    // colour takes its workgroup one round: 864 sites 2.7 us per sweep against
+    // 3.7, FP64 504 sites 4.4 against 5.8; beyond, sc 16^3 (2048) 5.2 against
+    // 3.8, FP64 8.5 against 4.9.
+    uint32_t most = 0;
+    uint64_t sites = 0;
+    for (const RepDev &R : h->reps) {
+        most = std::max(most, R.plane);
+        sites += R.n_box;
+    }
+    if (h->tile.kernel == KERNEL_LDS && most <= (h->prec == MC_F64 ? 640u : 1024u)) return;
+    if (sites > kTeamSites) return;
+    int dev = 0, cus = 0;
+    if (h->lds_max == 0 || hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (h->stream) { // a stream kept to part of the compute units
+        uint32_t mask[32] = {0};
+        if (hipExtStreamGetCUMask(h->stream, 32, mask) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        int n = 0;
+        for (uint32_t m : mask) n += __builtin_popcount(m);
+        if (n > 0) cus = std::min(cus, n);
+    }
+    const bool f64 = h->prec == MC_F64;
+    // the smallest share per workgroup whose launch fits the GPU kTeamShare
+    // times over
+    TeamPlan P;
+    bool found = false;
+    for (uint32_t q = 64; q <= 8192 && !found; q += q / 8) {
+        P = plan_teams(h, q);
+        // more planes per workgroup need more LDS and more rounds
+        if (!P.teams || P.lds > h->lds_max || P.phase_us > kTeamPhaseUs) return;
+        if (P.wgs.size() > (size_t)cus) continue;
+        int per_cu = 0;
+        if (team_allow(h->kind, f64, P.lds) != hipSuccess ||
+            team_slots(h->kind, f64, P.threads, P.lds, &per_cu) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        found = P.wgs.size() * kTeamShare <= (size_t)cus * (size_t)std::max(0, per_cu);
+    }
+    if (!found) return;
+    uint64_t o = 0;
+    const uint64_t n_state = 2 + 1 + (uint64_t)h->n_reps;
+    const uint64_t off_wgs = (o = align_up(sizeof(uint32_t) * n_state, 256));
+    const uint64_t off_words = (o = align_up(o + sizeof(TeamWg) * P.wgs.size(), 256));
+    const uint64_t off_part = (o = align_up(o + sizeof(uint64_t) * P.words, 256));
+    o += sizeof(double) * NQ * kTeamChunk * P.wgs.size();
+    if (hipMalloc((void **)&h->team_ws, o) != hipSuccess) {
+        (void)hipGetLastError();
+        h->team_ws = nullptr;
+        return;
+    }
+    h->team_state = (uint32_t *)h->team_ws;
+    h->team_wgs = (TeamWg *)(h->team_ws + off_wgs);
+    h->team_words = (uint64_t *)(h->team_ws + off_words);
+    h->team_partials = (double *)(h->team_ws + off_part);
+    h->team_grid = (uint32_t)P.wgs.size();
+    h->team_threads = P.threads;
+    h->team_lds = P.lds;
+    // tags start above the zeroed words
+    const uint64_t words32 = off_part / sizeof(uint32_t);
+    if (launch_zero_u32(h->team_state, (uint32_t)words32, h->stream) != hipSuccess ||
+        hipMemcpyAsync(h->team_wgs, P.wgs.data(), sizeof(TeamWg) * P.wgs.size(),
+                       hipMemcpyHostToDevice, h->stream) != hipSuccess ||
+        hipStreamSynchronize(h->stream) != hipSuccess) {
+        (void)hipGetLastError();
+        team_release(h);
+        return;
+    }
+    h->team_on = true;
+}
+
+void team_release(mc_sim *h)
+{
+    if (h->team_ws) (void)hipFree(h->team_ws);
+    h->team_ws = nullptr;
+    h->team_on = false;
+}
+
+mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool to_host)
+{
+    TeamLaunch L;
+    L.reps_dev = h->reps_dev;
+    L.wgs = h->team_wgs;
+    L.words = h->team_words;
+    L.epoch = h->team_state;
+    L.abort = h->team_state + 1;
+    L.done = h->team_state + 2;
+    L.host_flag = const_cast<uint32_t *>(h->host_flag);
+    L.tctr_dev = h->tctr;
+    L.partials = h->team_partials;
+    L.records = h->records;
+    L.n_reps = (uint32_t)h->n_reps;
+    L.seed_lo = (uint32_t)h->seed;
+    L.seed_hi = (uint32_t)(h->seed >> 32);
+    L.ring = kRing;
+    L.spin_limit = kTeamSpins;
+    for (uint32_t done = 0; done < n;) {
+        const uint32_t k = std::min(measure ? kTeamChunk : kTeamLong, n - done);
+        L.n_sweeps = k;
+        L.slot0 = (slot0 + done) % kRing;
+        L.host_last = measure && to_host && done + k == n ? h->host_last : nullptr;
+        HIP_TRY(launch_team(h->kind, h->prec == MC_F64, measure, L, h->team_grid, h->team_threads,
+                            h->team_lds, h->stream));
+        done += k;
+    }
+    return MC_OK;
+}
+
+} // namespace mcabi

@@ -16,7 +16,9 @@ namespace {
 
 // Candidate shapes for the autotuner: each kernel family with a few tile
 // widths, rows per thread and plane chunks aimed at 2k .. 24k workgroups.
-std::vector<Tile> tile_candidates(const mc_sim *h)
+constexpr int32_t TEAM_CANDIDATE = -1; // the default tile, swept by teams
+
+std::vector<Tile> tile_candidates(const mc_sim *h, uint32_t flags)
 {
     int W = 1, Ly = 1;
     for (const auto &d : h->desc) {
@@ -93,7 +95,26 @@ std::vector<Tile> tile_candidates(const mc_sim *h)
             out.push_back(t);
         }
     }
+    // small lattices swept by teams: that default stands in for the narrowest
+    // workgroup (the LDS kernel's smallest, else the narrowest tile), so the
+    // chain advances by as many trial sweeps with and without it
+    if (h->team_ws && !(flags & MC_PERSISTENT) && !out.empty())
+        (lds_fits(h) ? out.front() : out.back()) = Tile{TEAM_CANDIDATE, 0, 0, 0};
     return out;
+}
+
+// Choose a tile; the teams run whenever the choice is the handle's default.
+mc_status choose_tile(mc_sim *h, const Tile &t, bool teams)
+{
+    const Tile d = t.kernel == TEAM_CANDIDATE ? h->default_tile : t;
+    const mc_status st = mc_set_tile(h, d.kernel, d.tx, d.ty, d.zc);
+    if (st == MC_OK) h->team_on = teams && h->team_ws;
+    return st;
+}
+
+bool same_tile(const Tile &a, const Tile &b)
+{
+    return a.kernel == b.kernel && a.tx == b.tx && a.ty == b.ty && a.zc == b.zc;
 }
 
 std::string tune_key(const mc_sim *h, uint32_t flags)
@@ -182,22 +203,25 @@ mc_status mc_autotune(mc_sim *h, uint32_t trial_sweeps, uint32_t flags, const ch
         }
     }
     if (found) {
-        mc_status st = mc_set_tile(h, best.kernel, best.tx, best.ty, best.zc);
-        if (st != MC_OK) found = false; // stale entry: tune again
+        const bool teams = same_tile(best, h->default_tile) && !(flags & MC_PERSISTENT);
+        if (choose_tile(h, best, teams) != MC_OK) found = false; // stale entry: tune again
     }
     if (!found) {
         hipEvent_t e0, e1;
         HIP_TRY(hipEventCreate(&e0));
         HIP_TRY(hipEventCreate(&e1));
         double best_ms = 1e300;
-        for (const Tile &t : tile_candidates(h)) {
-            if ((flags & MC_PERSISTENT) && !persistent_supported(t)) continue;
-            if (mc_set_tile(h, t.kernel, t.tx, t.ty, t.zc) != MC_OK) continue; // e.g. too big
+        for (const Tile &t : tile_candidates(h, flags)) {
+            const bool team = t.kernel == TEAM_CANDIDATE;
+            const Tile &run = team ? h->default_tile : t;
+            if ((flags & MC_PERSISTENT) && !persistent_supported(run)) continue;
+            if (choose_tile(h, t, team) != MC_OK) continue; // e.g. too big
             // launch modes to time: as asked, or (MC_TUNED_LAUNCH) both
             for (int mode = 0; mode < 2; ++mode) {
                 uint32_t f = flags & ~MC_TUNED_LAUNCH;
                 if (mode == 1) {
-                    if (!tune_launch || !persistent_supported(t) || t.kernel == KERNEL_LDS) break;
+                    if (!tune_launch || !persistent_supported(run) || run.kernel == KERNEL_LDS)
+                        break;
                     f |= MC_PERSISTENT;
                 }
                 mc_status st = mc_sweep(h, 1, f);
@@ -227,8 +251,9 @@ mc_status mc_autotune(mc_sim *h, uint32_t trial_sweeps, uint32_t flags, const ch
         }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
-        mc_status st = mc_set_tile(h, best.kernel, best.tx, best.ty, best.zc);
+        const mc_status st = choose_tile(h, best, best.kernel == TEAM_CANDIDATE);
         if (st != MC_OK) return st;
+        best = h->tile;
         if (cache_path) {
             std::ofstream out(cache_path, std::ios::app);
             if (out) {

@@ -193,6 +193,22 @@ __device__ __forceinline__ uint32_t xcd_id()
     return v & 7u;
 }
 
+// Division by a divisor fixed for the launch (a lattice edge d >= 1):
+// floor(n / d) = mulhi(n, ceil(2^32 / d)), exact while n d < 2^32, which the
+// site indices of a lattice held in LDS (n below its few thousand box sites)
+// always satisfy.  Replaces the integer division sequence in the site loop.
+struct FastDiv {
+    uint32_t d, m;
+};
+__device__ __forceinline__ FastDiv fast_div(uint32_t d)
+{
+    return FastDiv{d, d <= 1u ? 0u : (uint32_t)((0x100000000ull + d - 1u) / d)};
+}
+__device__ __forceinline__ uint32_t div_of(uint32_t n, FastDiv f)
+{
+    return f.d <= 1u ? n : __umulhi(n, f.m);
+}
+
 // Exchange of two doubles between lane halves (HALF = 32: upper half of a with
 // lower half of b; HALF = 16: odd rows of a with even rows of b), and the sum
 // of the exchanged pair: each half (row) then holds one of the two operands,
@@ -268,17 +284,26 @@ __device__ __forceinline__ void block_store_partials(double (&a)[Q_N], double *d
     if (threadIdx.x >= Q_N && threadIdx.x < NQ) dst[threadIdx.x] = 0.0;
 }
 
-// One Metropolis attempt with local field h (J already applied) from the
-// words w of its Philox block: proposal from w0, w1, acceptance uniform from
-// w2.  Returns the final spin in (sx, sy, sz).
-template <typename T>
-__device__ __forceinline__ bool metropolis_words(const Words &w, T &sx, T &sy, T &sz, T hx, T hy,
-                                                 T hz, T K, T ex, T ey, T ez, T beta, bool greedy,
-                                                 T &dH)
+// The proposal of one attempt, which depends on its Philox words only: the
+// new direction from w0, w1 and the acceptance uniform from w2.
+template <typename T> struct Proposal {
+    T nx, ny, nz, P;
+};
+template <typename T> __device__ __forceinline__ Proposal<T> propose(const Words &w)
 {
-    T nx, ny, nz;
-    sphere_point(uniform23<T>(w.w0), uniform23<T>(w.w1), nx, ny, nz);
-    const T P = uniform23<T>(w.w2);
+    Proposal<T> q;
+    sphere_point(uniform23<T>(w.w0), uniform23<T>(w.w1), q.nx, q.ny, q.nz);
+    q.P = uniform23<T>(w.w2);
+    return q;
+}
+
+// Its decision with local field h (J already applied).  Returns whether the
+// move is accepted, and the final spin in (sx, sy, sz).
+template <typename T>
+__device__ __forceinline__ bool decide(const Proposal<T> &q, T &sx, T &sy, T &sz, T hx, T hy, T hz,
+                                       T K, T ex, T ey, T ez, T beta, bool greedy, T &dH)
+{
+    const T nx = q.nx, ny = q.ny, nz = q.nz;
     const T dx = nx - sx, dy = ny - sy, dz = nz - sz;
     const T pn = nx * ex + ny * ey + nz * ez;
     const T po = sx * ex + sy * ey + sz * ez;
@@ -286,7 +311,7 @@ __device__ __forceinline__ bool metropolis_words(const Words &w, T &sx, T &sy, T
     dH = -(hx * dx + hy * dy + hz * dz) - K * ((pn - po) * (pn + po));
     // Non-short-circuit: both comparisons stay lane masks, combined with the
     // uniform greedy flag by scalar mask operations.
-    const bool acc = (dH <= T(0)) | (below_exp(P, -beta * dH) & !greedy);
+    const bool acc = (dH <= T(0)) | (below_exp(q.P, -beta * dH) & !greedy);
     if (acc) {
         const T inv = inv_norm(nx * nx + ny * ny + nz * nz);
         sx = nx * inv;
@@ -294,6 +319,15 @@ __device__ __forceinline__ bool metropolis_words(const Words &w, T &sx, T &sy, T
         sz = nz * inv;
     }
     return acc;
+}
+
+// One Metropolis attempt from the words w of its Philox block.
+template <typename T>
+__device__ __forceinline__ bool metropolis_words(const Words &w, T &sx, T &sy, T &sz, T hx, T hy,
+                                                 T hz, T K, T ex, T ey, T ez, T beta, bool greedy,
+                                                 T &dH)
+{
+    return decide<T>(propose<T>(w), sx, sy, sz, hx, hy, hz, K, ex, ey, ez, beta, greedy, dH);
 }
 
 // The attempt of a colour pass: canonical site s, replica rid and sweep t key

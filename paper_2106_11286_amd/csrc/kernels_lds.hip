@@ -17,22 +17,6 @@ namespace mc {
 // ---------------------------------------------------------------------------
 template <typename T> using lptr = __attribute__((address_space(3))) T *;
 
-// Division by a divisor fixed for the launch (a lattice edge d >= 1):
-// floor(n / d) = mulhi(n, ceil(2^32 / d)), exact while n d < 2^32, which the
-// site indices of a lattice held in LDS (n below its few thousand box sites)
-// always satisfy.  Replaces the integer division sequence in the site loop.
-struct FastDiv {
-    uint32_t d, m;
-};
-__device__ __forceinline__ FastDiv fast_div(uint32_t d)
-{
-    return FastDiv{d, d <= 1u ? 0u : (uint32_t)((0x100000000ull + d - 1u) / d)};
-}
-__device__ __forceinline__ uint32_t div_of(uint32_t n, FastDiv f)
-{
-    return f.d <= 1u ? n : __umulhi(n, f.m);
-}
-
 // Block reduction for up to 1024 threads into out[0..Q_N) (LDS); fixed order.
 __device__ __forceinline__ void block_reduce_1024(double (&a)[Q_N], double *out)
 {

@@ -95,6 +95,48 @@ hipError_t launch_lds(int kind, bool f64, bool measure, const LdsLaunch &L, int 
 // Allow the LDS kernels of one lattice kind and precision `bytes` of dynamic LDS.
 hipError_t lds_allow(int kind, bool f64, uint32_t bytes);
 
+// Whole sweeps of small replicas by teams of workgroups (kernels_team.hip): a
+// workgroup of at most TEAM_THREADS threads owns planes z0 .. z0+nz-1 of
+// replica rep in LDS.  Boundary planes travel through `words`: a slot per
+// boundary plane of a team ([colour][component words][site], 64-bit words).
+constexpr int TEAM_THREADS = 512;
+struct alignas(16) TeamWg {
+    uint32_t rep;
+    int32_t z0, nz;
+    int32_t z_lo, z_hi;     // planes below and above (wrapped), -1 beyond an open face
+    int32_t lo, hi;         // slots that hold them, -1: none (open face, or a team of one)
+    int32_t own_lo, own_hi; // slots of the own outer planes, -1: nobody reads it
+    uint32_t first, members; // the team's workgroups
+    uint32_t pad;
+    uint64_t words;         // the team's slot 0 (offset into TeamLaunch::words)
+};
+struct TeamLaunch {
+    const RepDev *reps_dev;
+    const TeamWg *wgs;
+    uint64_t *words;
+    uint32_t *done;          // [1 + n_reps] finished workgroups (zero between launches)
+    uint32_t *epoch;         // tags used so far
+    uint32_t *abort;         // epoch + 1 of a launch whose wait gave up
+    uint32_t *host_flag;     // host-visible: a wait gave up
+    uint32_t *tctr_dev;      // sweep counter (advanced by the launch)
+    double *partials;        // [n_sweeps][grid][NQ] (measured launches)
+    double *records;         // ring [ring][n_reps][NR]
+    double *host_last;       // host-visible records of the last sweep (or null)
+    uint32_t n_reps, n_sweeps, seed_lo, seed_hi, ring, slot0, spin_limit;
+};
+// LDS of a team workgroup: every colour of nz + 2 planes, three components.
+constexpr uint64_t team_lds_bytes(int kind, uint64_t plane_sites, int nz, int esz)
+{
+    return 3ull * (kind == SC ? 2u : (kind == BCC ? 2u : 4u)) * plane_sites * (uint64_t)(nz + 2) *
+           (uint64_t)esz;
+}
+hipError_t launch_team(int kind, bool f64, bool measure, const TeamLaunch &L, uint32_t grid,
+                       int threads, uint32_t lds_bytes, hipStream_t st);
+// Allow the team kernels of one lattice kind and precision `bytes` of dynamic LDS.
+hipError_t team_allow(int kind, bool f64, uint32_t bytes);
+// Team workgroups one CU holds at a time.
+hipError_t team_slots(int kind, bool f64, int threads, uint32_t lds_bytes, int *per_cu);
+
 // The fused simple-cubic sweep (kernel 9): both colours of one sweep in one
 // launch, from each replica's current buffer set (sx, sy, sz) into its second
 // set (ax, ay, az), measured or not; p.lds_bytes of dynamic LDS.

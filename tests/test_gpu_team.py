@@ -1,0 +1,140 @@
+"""Sweeps of small lattices by teams of workgroups: the chain is bitwise that
+of the pass kernels, the records agree to FP64 rounding."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    from paper_2106_11286_amd import mcheis
+
+    return mcheis
+
+
+# (kind, [L of each replica], mask, sphere radius, precision, plain tile): the
+# default handle runs teams, the other one the pass kernel of the tile
+CASES = {
+    "f64-one-plane-each": ("sc", [(16, 16, 16)], 7, 0.0, "f64", (16, 16, 2, 0)),
+    "open-odd-edges": ("sc", [(50, 37, 23)], 0, 0.0, "f32", (256, 2, 3, 2)),
+    "open-z-only": ("sc", [(40, 30, 9)], 3, 0.0, "f32", (64, 2, 4, 1)),
+    "ragged-last-member": ("sc", [(24, 24, 26)] * 11, 7, 0.0, "f32", (256, 2, 2, 2)),
+    "uneven-batch": ("sc", [(24, 24, 24), (6, 4, 2), (32, 16, 8), (8, 8, 40)], 7, 0.0, "f32",
+                     (16, 16, 2, 0)),
+    "two-planes": ("sc", [(40, 40, 2)], 7, 0.0, "f32", (256, 2, 1, 2)),
+    "sphere": ("sc", [(22, 20, 18)], 0, 8.1, "f64", (16, 16, 2, 0)),
+    "bcc": ("bcc", [(13, 11, 9), (14, 14, 14)], 7, 0.0, "f64", (16, 16, 2, 0)),
+    "bcc-open": ("bcc", [(20, 20, 7)], 1, 0.0, "f32", (64, 4, 2, 6)),
+    "fcc": ("fcc", [(12, 13, 11)], 7, 0.0, "f32", (64, 4, 2, 6)),
+    "fcc-particle": ("fcc", [(16, 16, 16)], 0, 7.3, "f64", (16, 16, 2, 0)),
+}
+
+
+def _pair(M, name, seed=23):
+    kind, Ls, mask, R, prec, (tx, ty, zc, kernel) = CASES[name]
+    reps = [M.Replica(kind=kind, L=L, periodic_mask=mask, sphere_radius=R, K=0.15,
+                      e=(0.3, 0.2, 0.9), T=0.8 + 0.3 * r, replica_id=r) for r, L in enumerate(Ls)]
+    a = M.Simulation(reps, precision=prec, seed=seed)
+    b = M.Simulation(reps, precision=prec, seed=seed)
+    b.set_tile(tx, ty, zc, kernel=kernel)
+    return a, b
+
+
+def _same_spins(a, b):
+    for r in range(a.n_reps):
+        for x, y in zip(a.to_natural(r), b.to_natural(r)):
+            assert np.array_equal(x.cpu().numpy(), y.cpu().numpy())
+
+
+def _same_obs(oa, ob):
+    for x, y in zip(oa, ob):
+        assert x["n_accepted"] == y["n_accepted"] and x["sweep"] == y["sweep"]
+        # sums of at most 1e5 terms of order 1 in another order
+        assert np.max(np.abs(x["M"] - y["M"])) <= 1e-12
+        assert abs(x["E"] - y["E"]) <= 1e-10 * max(1.0, abs(y["E"]))
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_team_sweeps_are_bitwise(M, name):
+    a, b = _pair(M, name)
+    for n, measure in ((1, True), (3, False), (2, True), (1, False)):
+        a.sweep(n, measure=measure)
+        b.sweep(n, measure=measure)
+    _same_spins(a, b)
+    _same_obs(a.observables(), b.observables())
+    st = a.measure_state()
+    assert [o["n_sites"] for o in st] == a.n_occ
+
+
+def test_team_records_and_replays(M):
+    """More measured sweeps than one launch takes, schedules replayed as
+    graphs with eager sweeps between the replays, and a resumed counter."""
+    a, b = _pair(M, "f64-one-plane-each")
+    a.sweep(130, measure=True)
+    b.sweep(130, measure=True)
+    _same_obs(a.observables(), b.observables())
+    for k in range(3):
+        ra = a.run_schedule([1.0 + 0.1 * k], n_equil=5, n_meas=70)
+        rb = b.run_schedule([1.0 + 0.1 * k], n_equil=5, n_meas=70)
+        assert np.array_equal(ra[..., 0:2], rb[..., 0:2])
+        assert np.max(np.abs(ra[..., 2:5] - rb[..., 2:5])) <= 1e-12
+        a.sweep(1 + k)
+        b.sweep(1 + k)
+        _same_obs(a.measure_state(), b.measure_state())
+    for s in (a, b):
+        s.set_sweep(3)
+        s.sweep(2, measure=True)
+    assert a.get_sweep() == 5
+    _same_spins(a, b)
+    _same_obs(a.observables(), b.observables())
+
+
+def test_team_exchange_and_tile_change(M):
+    """Replica exchange over team sweeps, and a tile set by hand afterwards."""
+    reps = [M.Replica(kind="sc", L=(16, 16, 16), K=0.05, T=1.3 + 0.05 * r, replica_id=r)
+            for r in range(6)]
+    a = M.Simulation(reps, precision="f32", seed=3)
+    b = M.Simulation(reps, precision="f32", seed=3)
+    b.set_tile(16, 16, 2, kernel=0)
+    for s in (a, b):
+        s.exchange_init()
+        s.exchange_sweep(5, 3)
+    assert a.exchange_state() == b.exchange_state()
+    _same_spins(a, b)
+    a.set_tile(256, 2, 2, kernel=2)
+    for s in (a, b):
+        s.exchange_sweep(2, 2)
+    assert a.exchange_state() == b.exchange_state()
+    _same_spins(a, b)
+
+
+def test_team_handles_side_by_side(M):
+    """Four handles on four streams, their launches interleaved."""
+    sims = [_pair(M, "uneven-batch", seed=s) for s in range(4)]
+    for _ in range(4):
+        for a, _b in sims:
+            a.sweep(20, measure=True)
+    for a, b in sims:
+        b.sweep(80, measure=True)
+        _same_spins(a, b)
+        _same_obs(a.observables(), b.observables())
+
+
+def test_team_autotune_keeps_the_chain(M, tmp_path):
+    """The autotuner times the teams among its candidates; the state after it
+    equals a plain run of as many sweeps, also from its cache."""
+    cache = str(tmp_path / "tune.txt")
+    rep = M.Replica(kind="sc", L=(24, 24, 24), K=0.1, T=1.2)
+    for _ in range(2):
+        a = M.Simulation([rep], precision="f32", seed=4)
+        a.autotune(trial_sweeps=2, measure=True, cache_path=cache)
+        a.sweep(3, measure=True)
+        b = M.Simulation([rep], precision="f32", seed=4)
+        b.set_tile(256, 2, 2, kernel=2)
+        b.sweep(a.get_sweep(), measure=True)
+        _same_spins(a, b)
+        _same_obs(a.observables(), b.observables())
