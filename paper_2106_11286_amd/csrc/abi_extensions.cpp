@@ -196,6 +196,11 @@ mc_status mc_block_steps(mc_sim *h, uint32_t n, uint32_t step0, uint32_t n_steps
     B.seed_hi = (uint32_t)(h->seed >> 32);
     B.count_conflicts = (flags & MC_BLOCK_CONFLICTS) ? 1 : 0;
     B.counts = (unsigned long long *)w;
+    // per-workgroup counts of a step: scratch of the from-scratch measurement,
+    // which no work enqueued beside this uses
+    static_assert(BLOCK_SLOTS * 4 * sizeof(uint32_t) <= sizeof(double) * 8 * MEASURE_BLOCKS,
+                  "block slots exceed their scratch region");
+    B.slots = (uint32_t *)(h->scratch + h->lay.off_measure);
     B.stage_idx = (uint32_t *)(w + 256);
     B.stage_spin = w + 256 + align_up(4 * nb_max, 256);
     if ((st = xchg_pull(h)) != MC_OK) return st; // current temperatures into h->reps

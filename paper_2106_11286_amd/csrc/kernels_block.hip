@@ -2,10 +2,23 @@
 // comparison with the colour sweep (simple cubic).  A step is two launches:
 // every block of n consecutive canonical sites picks one site and computes its
 // attempt from the state before the step, staging the accepted spin; then the
-// staged moves are written.
+// staged moves are written and the step's counts added up.
+//
+// Bound: the gather of seven scattered spins per attempt, about the whole
+// lattice through the L2 per step.  Each XCD takes a contiguous eighth of the
+// blocks, so its part of the lattice stays in its L2; the counts go to one
+// slot per workgroup and are summed by one workgroup of the second launch
+// (three same-address atomics per wave, 12.6 ns each in turn, took 155 us a
+// step at 128^3, n = 8, against 10 now); the divisions by the
+// lattice edges and by n are multiplications by host-made constants.
 #include "device_common.hpp"
 
 namespace mc {
+
+__device__ __forceinline__ uint32_t div31(uint32_t n, Div31 d)
+{
+    return d.d == 1u ? n : __umulhi(n, d.m) >> d.s;
+}
 
 __device__ __forceinline__ uint32_t block_pick(uint32_t k, uint32_t n, uint32_t n_box,
                                                uint32_t rid, uint32_t step, uint32_t k0,
@@ -27,17 +40,25 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_block_propose(BlockLaunch B)
 {
     const RepDev &R = B.rep;
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ uint32_t s_cnt[4][3];
+    // workgroups are dealt to the XCDs in turn: XCD g takes the g-th eighth of
+    // the chunks (a multiple of 8 workgroups)
+    const uint32_t per = gridDim.x >> 3;
+    const uint32_t chunk = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+    const uint32_t k_begin = chunk * B.chunk;
+    const uint32_t k_end = min(B.n_blocks, k_begin + B.chunk);
     uint32_t att = 0, acc = 0, conf = 0;
-    if (k < B.n_blocks) {
+    for (uint32_t k = k_begin + threadIdx.x; k < k_end; k += blockDim.x) {
         const int Lx = R.Lx, Ly = R.Ly, Lz = R.Lz;
         Words w;
         const uint32_t s = block_pick(k, B.n, R.n_box, R.rid, B.step, B.seed_lo, B.seed_hi, w);
-        const int x = (int)(s % (uint32_t)Lx), y = (int)((s / (uint32_t)Lx) % (uint32_t)Ly);
-        const int z = (int)(s / ((uint32_t)Lx * (uint32_t)Ly));
+        const uint32_t row = div31(s, B.d_lx), zz = div31(row, B.d_ly);
+        const int x = (int)(s - row * (uint32_t)Lx), y = (int)(row - zz * (uint32_t)Ly);
+        const int z = (int)zz;
         uint32_t out = 0xFFFFFFFFu;
         if (occupied(R, x, y, z, 0, 0, 0)) {
-            att = 1;
+            ++att;
+            bool hit = false;
             const T *gx = (const T *)R.sx, *gy = (const T *)R.sy, *gz = (const T *)R.sz;
             const bool px = R.pmask & 1u, py = R.pmask & 2u, pz = R.pmask & 4u;
             // neighbours -x, +x, -y, +y, -z, +z (missing across open faces)
@@ -62,14 +83,17 @@ __global__ void __launch_bounds__(256) k_block_propose(BlockLaunch B)
                 hx += gx[i];
                 hy += gy[i];
                 hz += gz[i];
-                if (B.count_conflicts && !conf) {
+                if (B.count_conflicts && !hit) {
+                    // a neighbour in this block is not its choice
                     const uint32_t qs = ((uint32_t)(c * Ly + b) * (uint32_t)Lx) + (uint32_t)a;
+                    const uint32_t kq = div31(qs, B.d_n);
                     Words w2;
-                    if (block_pick(qs / B.n, B.n, R.n_box, R.rid, B.step, B.seed_lo, B.seed_hi,
-                                   w2) == qs)
-                        conf = 1;
+                    if (kq != k && block_pick(kq, B.n, R.n_box, R.rid, B.step, B.seed_lo,
+                                              B.seed_hi, w2) == qs)
+                        hit = true;
                 }
             }
+            conf += hit ? 1u : 0u;
             const T J = (T)R.J;
             hx *= J;
             hy *= J;
@@ -79,7 +103,7 @@ __global__ void __launch_bounds__(256) k_block_propose(BlockLaunch B)
             T dH;
             if (metropolis_words<T>(w, sx, sy, sz, hx, hy, hz, (T)R.K, (T)R.e[0], (T)R.e[1],
                                     (T)R.e[2], (T)R.beta, R.greedy != 0, dH)) {
-                acc = 1;
+                ++acc;
                 out = i;
                 T *st = (T *)B.stage_spin + 3 * (size_t)k;
                 st[0] = sx;
@@ -89,23 +113,42 @@ __global__ void __launch_bounds__(256) k_block_propose(BlockLaunch B)
         }
         B.stage_idx[k] = out;
     }
-    // counts: wave sums, then one atomic per wave
+    // counts: wave sums, then the workgroup's slot
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         att += __shfl_xor(att, o, 64);
         acc += __shfl_xor(acc, o, 64);
         conf += __shfl_xor(conf, o, 64);
     }
-    if ((threadIdx.x & 63) == 0 && att) {
-        atomicAdd(B.counts + 0, (unsigned long long)att);
-        atomicAdd(B.counts + 1, (unsigned long long)acc);
-        atomicAdd(B.counts + 2, (unsigned long long)conf);
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        s_cnt[wave][0] = att;
+        s_cnt[wave][1] = acc;
+        s_cnt[wave][2] = conf;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        uint32_t v = 0;
+        for (int i = 0; i < 4; ++i) v += s_cnt[i][threadIdx.x];
+        B.slots[blockIdx.x * 4u + threadIdx.x] = v;
     }
 }
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_block_apply(BlockLaunch B)
 {
+    if (blockIdx.x + 1u == gridDim.x) {
+        // the last workgroup adds the step's counts to the totals: wave q sums
+        // count q over the slots
+        const uint32_t q = threadIdx.x >> 6;
+        if (q >= 3u) return;
+        unsigned long long v = 0;
+        for (uint32_t j = threadIdx.x & 63u; j < B.n_slots; j += 64u) v += B.slots[j * 4u + q];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+        if ((threadIdx.x & 63u) == 0) B.counts[q] += v;
+        return;
+    }
     const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= B.n_blocks) return;
     const uint32_t i = B.stage_idx[k];
@@ -116,16 +159,26 @@ __global__ void __launch_bounds__(256) k_block_apply(BlockLaunch B)
     ((T *)B.rep.sz)[i] = st[2];
 }
 
-hipError_t launch_block_step(bool f64, const BlockLaunch &B, hipStream_t st)
+hipError_t launch_block_step(bool f64, const BlockLaunch &L, hipStream_t st)
 {
-    if (B.n_blocks == 0) return hipSuccess;
-    const dim3 g((B.n_blocks + 255) / 256), b(256);
+    if (L.n_blocks == 0) return hipSuccess;
+    BlockLaunch B = L;
+    // a multiple of 8 workgroups, at most one slot each
+    uint32_t grid = (B.n_blocks + 255u) / 256u;
+    grid = (grid + 7u) / 8u * 8u;
+    if (grid > BLOCK_SLOTS) grid = BLOCK_SLOTS;
+    B.n_slots = grid;
+    B.chunk = (uint32_t)(((uint64_t)B.n_blocks + grid - 1u) / grid);
+    B.d_n = make_div31(B.n);
+    B.d_lx = make_div31((uint32_t)B.rep.Lx);
+    B.d_ly = make_div31((uint32_t)B.rep.Ly);
+    const dim3 g(grid), ga((B.n_blocks + 255u) / 256u + 1u), b(256);
     if (f64) {
         hipLaunchKernelGGL(k_block_propose<double>, g, b, 0, st, B);
-        hipLaunchKernelGGL(k_block_apply<double>, g, b, 0, st, B);
+        hipLaunchKernelGGL(k_block_apply<double>, ga, b, 0, st, B);
     } else {
         hipLaunchKernelGGL(k_block_propose<float>, g, b, 0, st, B);
-        hipLaunchKernelGGL(k_block_apply<float>, g, b, 0, st, B);
+        hipLaunchKernelGGL(k_block_apply<float>, ga, b, 0, st, B);
     }
     return hipGetLastError();
 }

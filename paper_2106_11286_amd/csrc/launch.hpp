@@ -177,7 +177,12 @@ struct BlockLaunch {
     uint32_t *stage_idx;            // [n_blocks] storage index of the accepted move, or ~0
     void *stage_spin;               // [n_blocks][3] of the precision's type
     unsigned long long *counts;     // attempts, accepted, conflicts (accumulated)
+    uint32_t *slots;                // [BLOCK_SLOTS][4] counts of a step per workgroup
+    // set by launch_block_step
+    uint32_t n_slots, chunk;        // workgroups of the first launch, blocks of each
+    Div31 d_n, d_lx, d_ly;
 };
+constexpr uint32_t BLOCK_SLOTS = 2048;
 hipError_t launch_block_step(bool f64, const BlockLaunch &B, hipStream_t st);
 
 // Observables of one replica's current state from scratch (independent of

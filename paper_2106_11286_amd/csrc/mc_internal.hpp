@@ -28,6 +28,20 @@ struct alignas(16) RepDev {
     uint32_t item_begin, item_end; // this replica's range in the work list
 };
 
+// Division of n < 2^31 by an invariant d < 2^31 as a high product and a shift:
+// with p = ceil(log2 d) >= 1 and m = floor(2^(31+p) / d) + 1 (below 2^32),
+// m d - 2^(31+p) <= d <= 2^p, so floor(n m / 2^(31+p)) = floor(n / d) (Granlund
+// and Montgomery, PLDI'94).  d = 1 is marked by the divisor itself.
+struct Div31 {
+    uint32_t d, m, s; // s = p - 1, the shift after the high word
+};
+inline Div31 make_div31(uint32_t d)
+{
+    uint32_t p = 1;
+    while (p < 31u && (1u << p) < d) ++p;
+    return Div31{d, d <= 1u ? 0u : (uint32_t)((1ull << (31u + p)) / d + 1u), p - 1u};
+}
+
 // One workgroup's work: replica and the origin of its tile.
 struct alignas(16) WorkItem {
     uint32_t rep;

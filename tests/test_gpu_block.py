@@ -84,3 +84,19 @@ def test_block_errors(M):
     assert M.LIB.mc_block_workspace(sim.handle, 8, ctypes.byref(need)) == 0
     small = torch.empty(int(need.value) - 256, dtype=torch.uint8, device="cuda")
     assert M.LIB.mc_block_steps(sim.handle, 8, 0, 1, 0, small.data_ptr(), small.numel()) == -3
+
+
+def test_block_many_blocks_per_workgroup(M):
+    """More blocks than the first launch has threads (blocks of one site on
+    541,440 sites, 265 blocks a workgroup): one step's counts and spins equal
+    the oracle's."""
+    L = (94, 80, 72)
+    sim = M.Simulation([M.Replica(kind="sc", L=L, K=0.2, e=(0.0, 0.6, 0.8), T=1.2)],
+                       precision="f64", seed=5)
+    sim.block_steps(1, 2, 1, conflicts=True, reset=True)
+    lat = O.Lattice(O.SC, *L)
+    p = O.Params(J=1.0, K=0.2, e=(0.0, 0.6, 0.8), T=1.2, seed=5)
+    s = O.init(lat, p)
+    assert list(sim.block_counts()) == BS.run(lat, p, s, 1, 2, 1).sum(0).tolist()
+    for a, b in zip(natural(sim), s):
+        assert np.max(np.abs(a - b)) <= 1e-12
