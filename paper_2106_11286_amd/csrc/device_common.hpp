@@ -193,6 +193,12 @@ __device__ __forceinline__ uint32_t xcd_id()
     return v & 7u;
 }
 
+// floor(n / d) for n < 2^31 (see make_div31).
+__device__ __forceinline__ uint32_t div31(uint32_t n, Div31 d)
+{
+    return d.d == 1u ? n : __umulhi(n, d.m) >> d.s;
+}
+
 // Division by a divisor fixed for the launch (a lattice edge d >= 1):
 // floor(n / d) = mulhi(n, ceil(2^32 / d)), exact while n d < 2^32, which the
 // site indices of a lattice held in LDS (n below its few thousand box sites)

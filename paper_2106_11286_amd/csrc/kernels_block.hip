@@ -15,11 +15,6 @@
 
 namespace mc {
 
-__device__ __forceinline__ uint32_t div31(uint32_t n, Div31 d)
-{
-    return d.d == 1u ? n : __umulhi(n, d.m) >> d.s;
-}
-
 __device__ __forceinline__ uint32_t block_pick(uint32_t k, uint32_t n, uint32_t n_box,
                                                uint32_t rid, uint32_t step, uint32_t k0,
                                                uint32_t k1, Words &w)
