@@ -424,6 +424,8 @@ PassLaunch pass_args(mc_sim *h, uint32_t item_base, uint32_t n_blocks, uint32_t 
     p.n_items = (uint32_t)h->work.size();
     p.tctr_dev = h->tctr;
     p.t_off = t_off;
+    p.tctr_next = nullptr;
+    p.t_inc = 0;
     p.seed_lo = (uint32_t)h->seed;
     p.seed_hi = (uint32_t)(h->seed >> 32);
     p.tile = h->pass_tile;
@@ -494,8 +496,43 @@ mc_status enqueue_lds(mc_sim *h, uint32_t n, bool measure, uint32_t slot0)
     return MC_OK;
 }
 
-// Enqueue n sweeps (passes, optional finalise into ring slots slot0.., then
-// the counter advance).  Pure launches: safe inside stream capture.
+// The finalise counts finished workgroups in its stage slots.
+hipError_t zero_stage(mc_sim *h)
+{
+    return launch_zero_u32((uint32_t *)h->stage, 2u * NQ * FIN_BLOCKS * (uint32_t)h->n_reps,
+                           h->stream);
+}
+
+// The pass of colour c of the next sweep: every colour reads a counter of its
+// own and leaves the next one's (pass_done).
+PassLaunch sweep_pass(mc_sim *h, int c)
+{
+    const bool last = c + 1 == h->n_colours;
+    PassLaunch p = pass_args(h, 0, (uint32_t)h->work.size(), 0);
+    p.tctr_dev = h->tctr + c;
+    p.tctr_next = h->tctr + (last ? 0 : c + 1);
+    p.t_inc = last ? 1u : 0u;
+    return p;
+}
+
+// Reduce a measured sweep's partials into record `slot`.  A workgroup takes
+// about 512 partial slots: fewer than that in all make one workgroup per
+// replica (no second step), 32 of them serve 16 k (464^3: 4.9 us as before).
+hipError_t finalize_sweep(mc_sim *h, uint32_t slot, uint32_t t_add, bool to_host)
+{
+    uint32_t most = 1;
+    for (const RepDev &R : h->reps) most = std::max(most, R.item_end - R.item_begin);
+    const uint64_t slots = (uint64_t)most * (uint32_t)h->n_colours;
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>(FIN_BLOCKS, (slots + 511) / 512);
+    return launch_finalize(h->reps_dev, h->n_reps, h->n_colours, blocks, h->partials,
+                           (uint32_t)h->work.size(), h->tctr, t_add,
+                           h->records + (size_t)(slot % kRing) * h->n_reps * NR, h->stage,
+                           to_host ? h->host_last : nullptr, h->stream);
+}
+
+// Enqueue n sweeps (passes, optional finalise into ring slots slot0..; to_host:
+// the last record also to pinned memory).  Pure launches: safe inside stream
+// capture.
 mc_status enqueue_sweeps(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool to_host = false)
 {
     if (h->team_on) return enqueue_team(h, n, measure, slot0, to_host);
@@ -504,22 +541,16 @@ mc_status enqueue_sweeps(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bo
     const uint32_t n_items = (uint32_t)h->work.size();
     const bool fused = h->tile.kernel == KERNEL_FUSED;
     for (uint32_t i = 0; i < n; ++i) {
-        const PassLaunch p = pass_args(h, 0, n_items, i);
         if (fused) {
-            HIP_TRY(launch_fused(f64, measure, p, h->stream));
+            HIP_TRY(launch_fused(f64, measure, pass_args(h, 0, n_items, i), h->stream));
             HIP_TRY(launch_swap_state(h->reps_dev, (uint32_t)h->n_reps, h->stream));
         } else {
             for (int c = 0; c < h->n_colours; ++c)
-                HIP_TRY(launch_pass(h->kind, f64, c, measure, 0, p, h->stream));
+                HIP_TRY(launch_pass(h->kind, f64, c, measure, 0, sweep_pass(h, c), h->stream));
         }
-        if (measure) {
-            const uint32_t slot = (slot0 + i) % kRing;
-            HIP_TRY(launch_finalize(h->reps_dev, h->n_reps, h->n_colours, h->partials, n_items,
-                                    h->tctr, i, h->records + (size_t)slot * h->n_reps * NR,
-                                    h->stage, h->stream));
-        }
+        if (measure) HIP_TRY(finalize_sweep(h, slot0 + i, fused ? i + 1 : 0, to_host && i + 1 == n));
     }
-    HIP_TRY(launch_advance(h->tctr, n, h->stream));
+    if (fused) HIP_TRY(launch_advance(h->tctr, n, h->stream));
     return MC_OK;
 }
 
@@ -1004,7 +1035,8 @@ mc_status mc_init_lattice(const mc_replica_desc *reps, int32_t n_reps, mc_precis
     if (hipMemcpyAsync(h->work_dev, h->work.data(), sizeof(WorkItem) * h->work.size(),
                        hipMemcpyHostToDevice, h->stream) != hipSuccess ||
         launch_set_counter(h->tctr, 0u, h->stream) != hipSuccess ||
-        launch_zero_u32(h->pstate, persist_state_words(n_reps), h->stream) != hipSuccess)
+        launch_zero_u32(h->pstate, persist_state_words(n_reps), h->stream) != hipSuccess ||
+        zero_stage(h) != hipSuccess)
         return cleanup(fail(MC_E_DEVICE, "upload failed: %s", hipGetErrorString(hipGetLastError())));
     if (init != MC_INIT_USER) {
         for (int r = 0; r < n_reps; ++r) {
@@ -1065,7 +1097,7 @@ mc_status mc_sweep(mc_sim *h, uint32_t n_sweeps, uint32_t flags)
     if (h->t + n_sweeps > 0xFFFFFFFFull) return fail(MC_E_STATE, "sweep counter would exceed 2^32-1");
     const bool measure = flags & MC_MEASURE;
     const uint32_t slot0 = (uint32_t)(h->n_measured % kRing);
-    const bool to_host = h->team_on && !(flags & MC_PERSISTENT);
+    const bool to_host = !(flags & MC_PERSISTENT) && (h->team_on || h->tile.kernel != KERNEL_LDS);
     mc_status s = (flags & MC_PERSISTENT)
                       ? enqueue_persistent(h, n_sweeps, measure, slot0)
                       : enqueue_sweeps(h, n_sweeps, measure, slot0, to_host);
@@ -1132,24 +1164,21 @@ mc_status mc_sweep_timed(mc_sim *h, uint32_t n_sweeps, uint32_t flags, double *p
     const uint32_t slot0 = (uint32_t)(h->n_measured % kRing);
     hipError_t err = hipEventRecord(ev[2 * n_pass], h->stream);
     for (uint32_t i = 0; i < n_sweeps && err == hipSuccess; ++i) {
-        const PassLaunch p = pass_args(h, 0, n_items, i);
         for (uint32_t c = 0; c < per_sweep && err == hipSuccess; ++c) {
             const uint32_t k = i * per_sweep + c;
             err = hipEventRecord(ev[2 * k], h->stream);
             if (err == hipSuccess)
-                err = fused ? launch_fused(f64, measure, p, h->stream)
-                            : launch_pass(h->kind, f64, (int)c, measure, 0, p, h->stream);
+                err = fused ? launch_fused(f64, measure, pass_args(h, 0, n_items, i), h->stream)
+                            : launch_pass(h->kind, f64, (int)c, measure, 0, sweep_pass(h, (int)c),
+                                          h->stream);
             if (err == hipSuccess) err = hipEventRecord(ev[2 * k + 1], h->stream);
             if (err == hipSuccess && fused)
                 err = launch_swap_state(h->reps_dev, (uint32_t)h->n_reps, h->stream);
         }
         if (measure && err == hipSuccess)
-            err = launch_finalize(h->reps_dev, h->n_reps, h->n_colours, h->partials, n_items,
-                                  h->tctr, i,
-                                  h->records + (size_t)((slot0 + i) % kRing) * h->n_reps * NR,
-                                  h->stage, h->stream);
+            err = finalize_sweep(h, slot0 + i, fused ? i + 1 : 0, false);
     }
-    if (err == hipSuccess) err = launch_advance(h->tctr, n_sweeps, h->stream);
+    if (err == hipSuccess && fused) err = launch_advance(h->tctr, n_sweeps, h->stream);
     if (err == hipSuccess) err = hipEventRecord(ev[2 * n_pass + 1], h->stream);
     if (err == hipSuccess) err = hipEventSynchronize(ev[2 * n_pass + 1]);
     if (err != hipSuccess) {
@@ -1578,6 +1607,7 @@ mc_status mc_set_tile(mc_sim *h, int32_t kernel, int32_t tx, int32_t ty, int32_t
     h->queues_dev = (uint32_t *)(h->scratch + lay.off_queues);
     h->last_slot = -1;
     HIP_TRY(launch_zero_u32(h->pstate, persist_state_words(h->n_reps), h->stream));
+    HIP_TRY(zero_stage(h));
     for (int r = 0; r < h->n_reps; ++r) {
         h->reps[r].item_begin = b[r];
         h->reps[r].item_end = e[r];

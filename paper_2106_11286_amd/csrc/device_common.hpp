@@ -185,6 +185,17 @@ __device__ __forceinline__ bool logical_item(const PassLaunch &P, uint32_t &item
     return l < P.n_blocks;
 }
 
+// Sweep counter of a colour pass, and what its launch leaves for the next one.
+// Each colour has a counter of its own: a pass reads its colour's and, when its
+// sites are done, writes the next colour's (after the last colour t + 1 into
+// the first's), so no launch writes what it reads and none is spent on
+// advancing a counter.
+__device__ __forceinline__ uint32_t pass_sweep(const PassLaunch &P) { return *P.tctr_dev + P.t_off; }
+__device__ __forceinline__ void pass_done(const PassLaunch &P, uint32_t t)
+{
+    if (P.tctr_next && blockIdx.x == 0 && threadIdx.x == 0) *P.tctr_next = t + P.t_inc;
+}
+
 // The XCD (0..7) the calling wave runs on (hardware register XCC_ID).
 __device__ __forceinline__ uint32_t xcd_id()
 {

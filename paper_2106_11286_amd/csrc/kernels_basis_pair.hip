@@ -9,7 +9,9 @@ __global__ void __launch_bounds__(256) k_basis_pair(PassLaunch P)
 {
     uint32_t item;
     if (!logical_item(P, item)) return;
-    basis_pair_body<KIND, B, T, MEASURE, MODE, RY>(P, item, *P.tctr_dev + P.t_off);
+    const uint32_t t = pass_sweep(P);
+    basis_pair_body<KIND, B, T, MEASURE, MODE, RY>(P, item, t);
+    pass_done(P, t);
 }
 
 template <int KIND, typename T, bool MEASURE, int MODE, int RY>

@@ -14,7 +14,9 @@ __global__ void __launch_bounds__(256) k_sc_tile(PassLaunch P, int colour)
 {
     uint32_t item;
     if (!logical_item(P, item)) return;
-    sc_tile_body<T, MEASURE, MODE>(P, colour, item, *P.tctr_dev + P.t_off);
+    const uint32_t t = pass_sweep(P);
+    sc_tile_body<T, MEASURE, MODE>(P, colour, item, t);
+    pass_done(P, t);
 }
 
 template <typename T, bool MEASURE, int MODE, int RY>
@@ -22,7 +24,9 @@ __global__ void __launch_bounds__(256) k_sc_strip(PassLaunch P, int colour)
 {
     uint32_t item;
     if (!logical_item(P, item)) return;
-    sc_strip_body<T, MEASURE, MODE, RY>(P, colour, item, *P.tctr_dev + P.t_off);
+    const uint32_t t = pass_sweep(P);
+    sc_strip_body<T, MEASURE, MODE, RY>(P, colour, item, t);
+    pass_done(P, t);
 }
 
 template <typename T, bool MEASURE, int MODE, int RY>
@@ -30,7 +34,9 @@ __global__ void __launch_bounds__(256) k_sc_band(PassLaunch P, int colour)
 {
     uint32_t item;
     if (!logical_item(P, item)) return;
-    sc_band_body<T, MEASURE, MODE, RY>(P, colour, item, *P.tctr_dev + P.t_off);
+    const uint32_t t = pass_sweep(P);
+    sc_band_body<T, MEASURE, MODE, RY>(P, colour, item, t);
+    pass_done(P, t);
 }
 
 template <typename T, bool MEASURE, int MODE, int RY>
@@ -38,7 +44,9 @@ __global__ void __launch_bounds__(256) k_sc_pair(PassLaunch P, int colour)
 {
     uint32_t item;
     if (!logical_item(P, item)) return;
-    sc_pair_body<T, MEASURE, MODE, RY>(P, colour, item, *P.tctr_dev + P.t_off);
+    const uint32_t t = pass_sweep(P);
+    sc_pair_body<T, MEASURE, MODE, RY>(P, colour, item, t);
+    pass_done(P, t);
 }
 
 template <typename T, bool MEASURE, int MODE, int RY>
@@ -46,7 +54,9 @@ __global__ void __launch_bounds__(256) k_sc_pband(PassLaunch P, int colour)
 {
     uint32_t item;
     if (!logical_item(P, item)) return;
-    sc_pband_body<T, MEASURE, MODE, RY>(P, colour, item, *P.tctr_dev + P.t_off);
+    const uint32_t t = pass_sweep(P);
+    sc_pband_body<T, MEASURE, MODE, RY>(P, colour, item, t);
+    pass_done(P, t);
 }
 
 template <typename T, bool MEASURE, int MODE, int PP>
@@ -54,7 +64,9 @@ __global__ void __launch_bounds__(256) k_sc_lband(PassLaunch P, int colour)
 {
     uint32_t item;
     if (!logical_item(P, item)) return;
-    sc_lband_body<T, MEASURE, MODE, PP>(P, colour, item, *P.tctr_dev + P.t_off);
+    const uint32_t t = pass_sweep(P);
+    sc_lband_body<T, MEASURE, MODE, PP>(P, colour, item, t);
+    pass_done(P, t);
 }
 
 template <int KIND, int B, typename T, bool MEASURE, int MODE>
@@ -62,7 +74,9 @@ __global__ void __launch_bounds__(256) k_basis_strip(PassLaunch P)
 {
     uint32_t item;
     if (!logical_item(P, item)) return;
-    basis_strip_body<KIND, B, T, MEASURE, MODE>(P, item, *P.tctr_dev + P.t_off);
+    const uint32_t t = pass_sweep(P);
+    basis_strip_body<KIND, B, T, MEASURE, MODE>(P, item, t);
+    pass_done(P, t);
 }
 
 template <int KIND, int B, typename T, bool MEASURE, int MODE>
@@ -70,7 +84,9 @@ __global__ void __launch_bounds__(256) k_basis_pass(PassLaunch P)
 {
     uint32_t item;
     if (!logical_item(P, item)) return;
-    basis_body<KIND, B, T, MEASURE, MODE>(P, item, *P.tctr_dev + P.t_off);
+    const uint32_t t = pass_sweep(P);
+    basis_body<KIND, B, T, MEASURE, MODE>(P, item, t);
+    pass_done(P, t);
 }
 
 // ---------------------------------------------------------------------------

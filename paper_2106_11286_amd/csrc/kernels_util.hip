@@ -153,62 +153,88 @@ k_layout_basis(RepDev R, int to_natural, T *nx, T *ny, T *nz)
 }
 
 // ---------------------------------------------------------------------------
-// Finalise, two launches: FIN_BLOCKS blocks per replica each sum a contiguous
-// share of the replica's partial slots (all passes) into a stage slot; then
-// one workgroup per replica sums the stage slots in index order and writes
-// the FP64 record.  The launch boundary orders the two steps, so no block
-// waits for, or publishes to, another; the result depends only on the work
-// list.
+// Finalise: `blocks` workgroups per replica each sum a contiguous share of the
+// replica's partial slots (all passes); with more than one, the last of them to
+// finish sums their shares in index order.  The result depends only on the
+// work list and the number of workgroups.
+//
+// One launch (4.5 us) where a second one for the last step cost as much again.
+// The shares travel as agent-scope atomic stores that their wave waits for
+// before it counts itself (at most 32 counts per replica): no fence, whose
+// write-back of the L2 in every workgroup once made a single launch 159 us on
+// 64 replicas.  The count is kept beside the replica's first share.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
-k_finalize_stage(const RepDev *__restrict__ reps, int n_colours,
-                 const double *__restrict__ partials, uint32_t n_items,
-                 double *__restrict__ stage)
+k_finalize(const RepDev *__restrict__ reps, int n_colours, uint32_t blocks,
+           const double *__restrict__ partials, uint32_t n_items,
+           const uint32_t *__restrict__ tctr, uint32_t t_add, double *stage,
+           double *__restrict__ records, double *host_last)
 {
-    const uint32_t r = blockIdx.x / FIN_BLOCKS, j = blockIdx.x % FIN_BLOCKS;
+    __shared__ double red[4][Q_N], out[Q_N];
+    __shared__ uint32_t s_last;
+    const uint32_t r = blockIdx.x / blocks, j = blockIdx.x % blocks, q = threadIdx.x;
     const RepDev &R = reps[r];
     const uint32_t n = R.item_end - R.item_begin;
-    const uint32_t b0 = R.item_begin + (uint32_t)(((uint64_t)n * j) / FIN_BLOCKS);
-    const uint32_t b1 = R.item_begin + (uint32_t)(((uint64_t)n * (j + 1)) / FIN_BLOCKS);
+    const uint32_t b0 = R.item_begin + (uint32_t)(((uint64_t)n * j) / blocks);
+    const uint32_t b1 = R.item_begin + (uint32_t)(((uint64_t)n * (j + 1)) / blocks);
     double a[Q_N] = {0, 0, 0, 0, 0, 0};
     for (int c = 0; c < n_colours; ++c)
         for (uint32_t it = b0 + threadIdx.x; it < b1; it += blockDim.x) {
             const double *p = partials + ((size_t)c * n_items + it) * NQ;
 #pragma unroll
-            for (int q = 0; q < Q_N; ++q) a[q] += p[q];
+            for (int i = 0; i < Q_N; ++i) a[i] += p[i];
         }
-    block_store_partials(a, stage + ((size_t)r * FIN_BLOCKS + j) * NQ);
-}
-
-__global__ void __launch_bounds__(64)
-k_finalize_record(const RepDev *__restrict__ reps, const uint32_t *__restrict__ tctr,
-                  uint32_t t_off, const double *__restrict__ stage, double *__restrict__ records)
-{
-    // lane q sums observable q over the stage slots in slot order; all its
-    // loads are issued before the first add
-    __shared__ double out[Q_N];
-    const uint32_t r = blockIdx.x, q = threadIdx.x;
-    const double *st = stage + (size_t)r * FIN_BLOCKS * NQ;
+    store_wave_sums(a, red[threadIdx.x >> 6]);
+    __syncthreads();
+    double *const share = stage + (size_t)r * FIN_BLOCKS * NQ;
     if (q < (uint32_t)Q_N) {
-        double v[FIN_BLOCKS];
+        double v = 0.0;
+        for (int w = 0; w < 4; ++w) v += red[w][q];
+        if (blocks == 1u) out[q] = v;
+        else
+            __hip_atomic_store(share + (size_t)j * NQ + q, v, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (blocks > 1u) {
+        if (q == 0) {
+            // the shares were stored by this wave
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt 0
+            uint32_t *const count = (uint32_t *)(share + NQ - 1);
+            const uint32_t old = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT);
+            s_last = old + 1u == blocks;
+            if (s_last)
+                __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (!s_last) return;
+        if (q < (uint32_t)Q_N) {
+            // every load is issued before the first add
+            double v[FIN_BLOCKS];
 #pragma unroll
-        for (uint32_t b = 0; b < FIN_BLOCKS; ++b) v[b] = st[b * NQ + q];
-        double sum = 0.0;
+            for (uint32_t b = 0; b < FIN_BLOCKS; ++b)
+                v[b] = b < blocks ? __hip_atomic_load(share + b * NQ + q, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT)
+                                  : 0.0;
+            double sum = 0.0;
 #pragma unroll
-        for (uint32_t b = 0; b < FIN_BLOCKS; ++b) sum += v[b];
-        out[q] = sum;
+            for (uint32_t b = 0; b < FIN_BLOCKS; ++b) sum += v[b];
+            out[q] = sum;
+        }
     }
     __syncthreads();
-    if (q != 0) return;
-    double *rec = records + (size_t)r * NR;
-    rec[R_MX] = out[Q_MX];
-    rec[R_MY] = out[Q_MY];
-    rec[R_MZ] = out[Q_MZ];
-    rec[R_EEX] = -out[Q_SH];
-    rec[R_EAN] = -reps[r].K * out[Q_PE2];
-    rec[R_NACC] = out[Q_NACC];
-    rec[R_SWEEP] = (double)(*tctr + t_off) + 1.0;
-    rec[7] = 0.0;
+    if (q >= (uint32_t)NR) return;
+    const double v = q == R_MX     ? out[Q_MX]
+                     : q == R_MY   ? out[Q_MY]
+                     : q == R_MZ   ? out[Q_MZ]
+                     : q == R_EEX  ? -out[Q_SH]
+                     : q == R_EAN  ? -R.K * out[Q_PE2]
+                     : q == R_NACC ? out[Q_NACC]
+                     : q == R_SWEEP ? (double)(*tctr + t_add)
+                                    : 0.0;
+    records[(size_t)r * NR + q] = v;
+    if (host_last) host_last[(size_t)r * NR + q] = v;
 }
 
 __global__ void k_advance(uint32_t *tctr, uint32_t n)
@@ -305,15 +331,15 @@ hipError_t launch_layout(bool f64, int kind, const RepDev *rep_host, bool to_nat
                                         (float *)nz, st);
 }
 
-hipError_t launch_finalize(const RepDev *reps_dev, int n_reps, int n_colours,
+hipError_t launch_finalize(const RepDev *reps_dev, int n_reps, int n_colours, uint32_t blocks,
                            const double *partials_dev, uint32_t n_items,
-                           const uint32_t *tctr_dev, uint32_t t_off, double *records_dev,
-                           double *stage_dev, hipStream_t st)
+                           const uint32_t *tctr_dev, uint32_t t_add, double *records_dev,
+                           double *stage_dev, double *host_last, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_finalize_stage, dim3(n_reps * FIN_BLOCKS), dim3(256), 0, st, reps_dev,
-                       n_colours, partials_dev, n_items, stage_dev);
-    hipLaunchKernelGGL(k_finalize_record, dim3(n_reps), dim3(64), 0, st, reps_dev, tctr_dev, t_off,
-                       stage_dev, records_dev);
+    if (blocks < 1u || blocks > FIN_BLOCKS) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_finalize, dim3((uint32_t)n_reps * blocks), dim3(256), 0, st, reps_dev,
+                       n_colours, blocks, partials_dev, n_items, tctr_dev, t_add, stage_dev,
+                       records_dev, host_last);
     return hipGetLastError();
 }
 

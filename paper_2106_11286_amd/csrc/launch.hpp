@@ -17,6 +17,8 @@ struct PassLaunch {
     uint32_t n_items;         // items in the whole work list (partials stride)
     const uint32_t *tctr_dev; // sweep counter t (device)
     uint32_t t_off;           // added to t
+    uint32_t *tctr_next;      // the next pass's counter, written t + t_inc (or null)
+    uint32_t t_inc;
     uint32_t seed_lo, seed_hi;
     Tile tile;
     double *partials_dev;     // [n_colours][n_items][NQ]
@@ -40,12 +42,15 @@ hipError_t launch_init(bool f64, int kind, const RepDev *rep_host, int mode, uin
 hipError_t launch_layout(bool f64, int kind, const RepDev *rep_host, bool to_natural, void *nx,
                          void *ny, void *nz, hipStream_t st);
 
-// Reduce partials of every pass into one record per replica (two launches).
-// stage_dev holds n_reps * FIN_BLOCKS * NQ doubles.
-hipError_t launch_finalize(const RepDev *reps_dev, int n_reps, int n_colours,
+// Reduce partials of every pass into one record per replica: one launch of
+// `blocks` (1 .. FIN_BLOCKS) workgroups per replica.  stage_dev holds
+// n_reps * FIN_BLOCKS * NQ doubles, zeroed once before its first use; the
+// record's sweep is *tctr_dev + t_add; host_last (or null) is host-visible
+// memory that gets the records too.
+hipError_t launch_finalize(const RepDev *reps_dev, int n_reps, int n_colours, uint32_t blocks,
                            const double *partials_dev, uint32_t n_items,
-                           const uint32_t *tctr_dev, uint32_t t_off, double *records_dev,
-                           double *stage_dev, hipStream_t st);
+                           const uint32_t *tctr_dev, uint32_t t_add, double *records_dev,
+                           double *stage_dev, double *host_last, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t *p, uint32_t n, hipStream_t st);
 
 // One persistent launch that runs n_sweeps sweeps of every replica.  Work units

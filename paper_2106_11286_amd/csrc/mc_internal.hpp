@@ -52,7 +52,7 @@ struct alignas(16) WorkItem {
 enum : int { Q_MX = 0, Q_MY, Q_MZ, Q_PE2, Q_SH, Q_NACC, Q_N };
 constexpr int NQ = 8; // padded slot width (doubles)
 
-// Workgroups per replica in the first stage of the observable finalise.
+// Most workgroups per replica in the observable finalise.
 constexpr uint32_t FIN_BLOCKS = 32;
 
 // Record written by the finalise kernel (FP64), per replica per measured sweep.
