@@ -130,15 +130,40 @@ uint64_t xy_tiles(const mc_replica_desc &d, const Tile &t)
     return (uint64_t)((row_len(d) + wx - 1) / wx) * ((d.Ly + t.ty - 1) / t.ty);
 }
 
-// Planes per workgroup so that a pass has about kTargetItems workgroups.
-int z_chunk(const mc_replica_desc *reps, int n, const Tile &t)
+// Planes per workgroup of a default tile.  Taller chunks share the halo planes
+// and the observable epilogue over more sites, shorter ones fill the GPU.
+// Measured (us per sweep, unmeasured / measured, workgroups of 256 threads):
+//  * a lattice whose workgroups all fit the GPU at once (about 1024 FP32, 512
+//    FP64) with at most 8 planes each does best as that one round: 32 x 64^3
+//    zc 1 62.8 / 86.1, zc 8 60.9 / 66.7; FP64 128^3 zc 1 42.4 / 56.6, zc 4
+//    35.9 / 43.0; bcc 128^3 zc 1 35.1 / 43.5, zc 4 30.4 / 37.6;
+//  * a larger one with about 6000 workgroups (FP64 3500): 302 x 251 x 210 zc 2
+//    104 / 120, zc 3 104 / 113, zc 5 115 / 119; 464^3 zc 14 803 / 805, zc 8
+//    766 / 780; FP64 464^3 zc 5 1576 / 1611, zc 16 1570 / 1582, zc 24 1576 / 1589.
+int z_chunk(const mc_replica_desc *reps, int n, const Tile &t, size_t esz)
 {
     uint64_t cols = 0, planes = 0;
+    bool sphere = false;
     for (int r = 0; r < n; ++r) {
         cols += xy_tiles(reps[r], t) * reps[r].Lz;
         planes = std::max<uint64_t>(planes, reps[r].Lz);
+        sphere |= reps[r].sphere_radius > 0.0;
     }
-    const uint64_t zc = (cols + kTargetItems - 1) / kTargetItems;
+    uint64_t zc;
+    if (t.kernel == KERNEL_LBAND) {
+        zc = (cols + kTargetItems - 1) / kTargetItems;
+    } else {
+        const bool f64 = esz == sizeof(double);
+        const bool flat = t.kernel == KERNEL_TILE; // tx * ty threads, else tx
+        const uint64_t threads = (uint64_t)t.tx * (uint64_t)(flat ? t.ty : 1);
+        const uint64_t p = std::max<uint64_t>(1, cols * threads / 256);
+        const uint64_t round = f64 ? 512 : 1024, many = f64 ? 3500 : 6000;
+        zc = (p + round - 1) / round;
+        if (zc > 8) zc = (p + many / 2) / many;
+        // a sphere leaves about half of its box's rows empty or short (fcc
+        // 128^3, R = 60: zc 4 68.7 / 77.4, zc 2 65.8 / 75.2)
+        if (sphere) zc = (zc + 1) / 2;
+    }
     return (int)std::max<uint64_t>(1, std::min<uint64_t>(zc, planes));
 }
 
@@ -165,18 +190,34 @@ Tile default_tile(const mc_replica_desc *reps, int n, size_t esz)
         Ly = std::max(Ly, reps[r].Ly);
     }
     Tile t;
-    bool sphere = false; // only the tile kernel masks unoccupied simple-cubic sites
-    for (int r = 0; r < n; ++r) sphere |= reps[r].kind == MC_SC && reps[r].sphere_radius > 0.0;
+    bool cut = false;
+    for (int r = 0; r < n; ++r) cut |= reps[r].sphere_radius > 0.0;
+    // only the tile kernel masks unoccupied simple-cubic sites
+    const bool sphere = cut && reps[0].kind == MC_SC;
     bool fits = !sphere; // the strip kernel addresses each component array with 32-bit offsets
     for (int r = 0; r < n; ++r) fits &= box_sites(reps[r]) * esz <= 0xFFFFFFFFull;
     bool even = true; // every row holds an even number of packed columns (sc) or cells
     for (int r = 0; r < n; ++r) even &= row_len(reps[r]) % 2 == 0;
-    if (reps[0].kind == MC_SC && fits && even && Wmin >= 96) {
-        // long rows: two columns per thread, 2 rows per thread, whole rows
-        // (up to 512 columns) per workgroup
+    // lanes of the pair kernel that hold a pair of columns
+    const int pair_tx = std::min(256, ((W + 1) / 2 + 63) / 64 * 64);
+    uint64_t pairs = 0, lanes = 0, bytes = 0;
+    for (int r = 0; r < n; ++r) {
+        const uint64_t np = (uint64_t)row_len(reps[r]) / 2, rows = (uint64_t)reps[r].Ly * reps[r].Lz;
+        pairs += np * rows;
+        lanes += (np + pair_tx - 1) / pair_tx * pair_tx * rows;
+        bytes += 3 * esz * box_sites(reps[r]);
+    }
+    if (reps[0].kind == MC_SC && fits && even && Wmin >= 96 && 5 * pairs >= 4 * lanes) {
+        // long rows: two columns per thread, whole rows (up to 512 columns)
+        // per workgroup, where at least 0.8 of the lanes have work (320^3:
+        // 0.62, pair 313 / 326 us per sweep, bands 252 / 265).  Two rows per
+        // thread where the state exceeds the 256 MB cache (464^3 766 / 780 us,
+        // one row above 798), one where it does not or in FP64, for the
+        // waves its registers allow (256^3 105 / 118 -> 94 / 103 us, FP64
+        // 321 / 336 -> 257 / 268, FP64 464^3 1790 / 1862 -> 1570 / 1582).
         t.kernel = KERNEL_PAIR;
-        t.tx = std::min(256, ((W + 1) / 2 + 63) / 64 * 64);
-        t.ty = 2;
+        t.tx = pair_tx;
+        t.ty = esz == sizeof(double) || bytes <= 256000000ull ? 1 : 2;
     } else if (reps[0].kind == MC_SC && fits) {
         // bands of 2 rows, (band, column) positions dealt to 256 threads
         t.kernel = KERNEL_BAND;
@@ -189,17 +230,21 @@ Tile default_tile(const mc_replica_desc *reps, int n, size_t esz)
         t.tx = 256;
         t.ty = std::max(1, std::min(64, 256 / std::max(1, W / 2)));
     } else if (reps[0].kind != MC_SC && fits && even) {
-        // bcc / fcc: bands of cell pairs (fcc keeps one row per band: three
-        // other bases' rows in registers)
+        // bcc / fcc: bands of cell pairs.  fcc keeps one row per band (three
+        // other bases' rows in registers), and so does bcc in FP64 (200^3 290
+        // -> 250 us) or from the 256 MB cache (128^3 31.3 / 38.2 -> 30.4 / 37.6
+        // us); beyond, two rows re-read less (368^3 743 / 752 -> 733 / 750 us).
+        // One wave per workgroup where a sphere leaves rows to drop (fcc 128^3,
+        // R = 60: 66.5 / 82.5 -> 65.8 / 75.2).
         t.kernel = KERNEL_BPAIR;
-        t.tx = 256;
-        t.ty = reps[0].kind == MC_FCC ? 1 : 2;
+        t.tx = cut ? 64 : 256;
+        t.ty = reps[0].kind == MC_FCC || esz == sizeof(double) || bytes <= 256000000ull ? 1 : 2;
     } else {
         t.kernel = KERNEL_TILE;
         t.tx = std::min(64, pow2_at_least(W));
         t.ty = std::min(256 / t.tx, pow2_at_least(Ly));
     }
-    t.zc = z_chunk(reps, n, t);
+    t.zc = z_chunk(reps, n, t, esz);
     return t;
 }
 
@@ -292,6 +337,9 @@ void make_work(const mc_replica_desc *reps, int n, const Tile &t, std::vector<Wo
     work.clear();
     begin.assign(n, 0);
     end.assign(n, 0);
+    uint64_t most = 0;
+    for (int r = 0; r < n; ++r) most += xy_tiles(reps[r], t) * ((reps[r].Lz + t.zc - 1) / t.zc);
+    work.reserve(most);
     for (int r = 0; r < n; ++r) {
         const mc_replica_desc &d = reps[r];
         begin[r] = (uint32_t)work.size();
