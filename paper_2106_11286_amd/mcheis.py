@@ -299,13 +299,19 @@ def obs_to_dict(o: Obs) -> dict:
             "E_anis": o.E_anis}
 
 
+# memory layout of ``Obs``
+_OBS_DTYPE = np.dtype([("sweep", "<u8"), ("n_sites", "<u8"), ("n_accepted", "<u8"),
+                       ("M", "<f8", (3,)), ("absM", "<f8"), ("E", "<f8"), ("E_exch", "<f8"),
+                       ("E_anis", "<f8")])
+
+
 def obs_array_to_numpy(arr, n) -> np.ndarray:
     """(n, 10) float64: sweep, n_accepted, Mx, My, Mz, |M|, E, E_exch, E_anis, n_sites."""
+    a = np.frombuffer(arr, dtype=_OBS_DTYPE, count=n) if n else np.empty(0, _OBS_DTYPE)
     out = np.empty((n, 10))
-    for i in range(n):
-        o = arr[i]
-        out[i] = (o.sweep, o.n_accepted, o.M[0], o.M[1], o.M[2], o.absM, o.E, o.E_exch,
-                  o.E_anis, o.n_sites)
+    out[:, 0], out[:, 1], out[:, 2:5] = a["sweep"], a["n_accepted"], a["M"]
+    out[:, 5], out[:, 6], out[:, 7] = a["absM"], a["E"], a["E_exch"]
+    out[:, 8], out[:, 9] = a["E_anis"], a["n_sites"]
     return out
 
 
