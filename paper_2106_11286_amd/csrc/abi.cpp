@@ -583,7 +583,8 @@ hipError_t finalize_sweep(mc_sim *h, uint32_t slot, uint32_t t_add, bool to_host
 // capture.
 mc_status enqueue_sweeps(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool to_host = false)
 {
-    if (h->team_on) return enqueue_team(h, n, measure, slot0, to_host);
+    if (h->team_on)
+        return enqueue_team(h, n, measure, slot0, to_host ? TeamHost::last : TeamHost::none);
     if (h->tile.kernel == KERNEL_LDS) return enqueue_lds(h, n, measure, slot0);
     const bool f64 = h->prec == MC_F64;
     const uint32_t n_items = (uint32_t)h->work.size();
@@ -698,7 +699,7 @@ bool persistent_supported(const Tile &t)
 mc_status enqueue_persistent(mc_sim *h, uint32_t n, bool measure, uint32_t slot0)
 {
     if (h->tile.kernel == KERNEL_LDS)
-        return h->team_on ? enqueue_team(h, n, measure, slot0, false)
+        return h->team_on ? enqueue_team(h, n, measure, slot0, TeamHost::none)
                           : enqueue_lds(h, n, measure, slot0);
     if (!persistent_supported(h->tile))
         return fail(MC_E_UNSUPPORTED, "persistent sweeps: no kernel for this tile (%d rows "
@@ -859,6 +860,10 @@ void note_sweeps(mc_sim *h, uint64_t n)
 mc_status run_chunk(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool persistent)
 {
     if (n == 0) return MC_OK;
+    // a chunk of team sweeps is one launch, which leaves its records in pinned
+    // memory: nothing to replay or to copy
+    if (h->team_on && (!persistent || h->tile.kernel == KERNEL_LDS))
+        return enqueue_team(h, n, measure, slot0, TeamHost::all);
     if (!h->stream) {
         const mc_status s = persistent ? enqueue_persistent(h, n, measure, slot0)
                                        : enqueue_sweeps(h, n, measure, slot0);
@@ -1178,7 +1183,7 @@ mc_status mc_sweep_timed(mc_sim *h, uint32_t n_sweeps, uint32_t flags, double *p
         const uint32_t slot0 = (uint32_t)(h->n_measured % kRing);
         hipError_t err = hipEventRecord(e0, h->stream);
         mc_status st = err != hipSuccess ? MC_OK
-                       : h->team_on      ? enqueue_team(h, n_sweeps, measure, slot0, false)
+                       : h->team_on      ? enqueue_team(h, n_sweeps, measure, slot0, TeamHost::none)
                                          : enqueue_lds(h, n_sweeps, measure, slot0);
         if (err == hipSuccess && st == MC_OK) err = hipEventRecord(e1, h->stream);
         if (err == hipSuccess && st == MC_OK) err = hipEventSynchronize(e1);
@@ -1372,7 +1377,12 @@ mc_status mc_run_schedule(mc_sim *h, const mc_schedule *s, mc_obs *series, uint6
         if (!(s->T[i] >= 0.0)) return fail(MC_E_ARG, "schedule T[%lld] must be >= 0", (long long)i);
     uint64_t written = 0;
     for (int step = 0; step < s->n_T; ++step) {
-        mc_status st = mc_set_temperatures(h, s->T + (size_t)step * h->n_reps, h->n_reps);
+        // the descriptors are uploaded only when a temperature changes (or a
+        // replica exchange, which moves them on the device, has to end)
+        const double *T = s->T + (size_t)step * h->n_reps;
+        bool same = !h->xchg_active;
+        for (int r = 0; r < h->n_reps; ++r) same = same && h->desc[r].T == T[r];
+        mc_status st = same ? MC_OK : mc_set_temperatures(h, T, h->n_reps);
         if (st != MC_OK) return st;
         for (uint32_t done = 0; done < s->n_equil;) {
             const uint32_t k = std::min(kGraphChunk, s->n_equil - done);
@@ -1389,7 +1399,9 @@ mc_status mc_run_schedule(mc_sim *h, const mc_schedule *s, mc_obs *series, uint6
             h->last_on_host = false;
             h->last_slot = k - 1;
             const size_t sz = sizeof(double) * NR * h->n_reps * k;
-            HIP_TRY(hipMemcpyAsync(h->host_rec, h->records, sz, hipMemcpyDeviceToHost, h->stream));
+            if (!h->team_on || (persistent && h->tile.kernel != KERNEL_LDS))
+                HIP_TRY(hipMemcpyAsync(h->host_rec, h->records, sz, hipMemcpyDeviceToHost,
+                                       h->stream));
             HIP_TRY(hipStreamSynchronize(h->stream));
             if ((st = check_persistent(h)) != MC_OK) return st;
             for (uint32_t j = 0; j < k; ++j, ++meas_idx) {

@@ -37,7 +37,7 @@ constexpr uint32_t kRing = 256;       // observable records kept per replica
 // LDS kept back from the dynamic allocation of the LDS kernel for its static
 // arrays (reduction slots).
 constexpr uint32_t kLdsReserve = 2048;
-constexpr uint32_t kTargetItems = 8192; // work items aimed for per pass
+constexpr uint32_t kTargetItems = 8192; // work items aimed for per pass (LDS-staged bands)
 constexpr uint32_t kGraphChunk = 64;  // sweeps per captured graph
 
 struct ScratchLayout {
@@ -130,7 +130,10 @@ bool lds_fits(const mc_sim *h);
 // (leaves team_ws null otherwise); release it; enqueue n sweeps.
 void team_init(mc_sim *h);
 void team_release(mc_sim *h);
-mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool to_host);
+// Records of a measured team launch in pinned memory besides the device ring:
+// none, the last sweep's (host_last), or all at their ring slots (host_rec).
+enum class TeamHost { none, last, all };
+mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, TeamHost host);
 // A simple-cubic handle with a replica cut to a sphere (tile and LDS kernels only).
 bool sc_sphere(const mc_sim *h);
 mc_status check_persistent(mc_sim *h);

@@ -188,7 +188,7 @@ void team_release(mc_sim *h)
     h->team_on = false;
 }
 
-mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool to_host)
+mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, TeamHost host)
 {
     TeamLaunch L;
     L.reps_dev = h->reps_dev;
@@ -210,7 +210,8 @@ mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool
         const uint32_t k = std::min(measure ? kTeamChunk : kTeamLong, n - done);
         L.n_sweeps = k;
         L.slot0 = (slot0 + done) % kRing;
-        L.host_last = measure && to_host && done + k == n ? h->host_last : nullptr;
+        L.host_last = measure && host == TeamHost::last && done + k == n ? h->host_last : nullptr;
+        L.host_ring = measure && host == TeamHost::all ? h->host_rec : nullptr;
         HIP_TRY(launch_team(h->kind, h->prec == MC_F64, measure, L, h->team_grid, h->team_threads,
                             h->team_lds, h->stream));
         done += k;

@@ -394,7 +394,9 @@ __global__ void __launch_bounds__(TEAM_THREADS, sizeof(T) == 8 ? 2 : 4) k_team_s
             if (i == (uint32_t)R_EAN) v = -Kd * v;
             if (i == (uint32_t)R_SWEEP) v = (double)(t0 + sw) + 1.0;
             if (i == 7u) v = 0.0;
-            L.records[((size_t)((L.slot0 + sw) % L.ring) * L.n_reps + w.rep) * NR + i] = v;
+            const size_t at = ((size_t)((L.slot0 + sw) % L.ring) * L.n_reps + w.rep) * NR + i;
+            L.records[at] = v;
+            if (L.host_ring) L.host_ring[at] = v;
             if (L.host_last && sw + 1u == L.n_sweeps) L.host_last[(size_t)w.rep * NR + i] = v;
         }
     }

@@ -127,6 +127,7 @@ struct TeamLaunch {
     double *partials;        // [n_sweeps][grid][NQ] (measured launches)
     double *records;         // ring [ring][n_reps][NR]
     double *host_last;       // host-visible records of the last sweep (or null)
+    double *host_ring;       // host-visible copy of the ring (or null)
     uint32_t n_reps, n_sweeps, seed_lo, seed_hi, ring, slot0, spin_limit;
 };
 // LDS of a team workgroup: every colour of nz + 2 planes, three components.
