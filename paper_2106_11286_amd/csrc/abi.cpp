@@ -337,7 +337,7 @@ void make_work(const mc_replica_desc *reps, int n, const Tile &t, std::vector<Wo
     work.clear();
     begin.assign(n, 0);
     end.assign(n, 0);
-    uint64_t most = 0;
+    uint64_t most = 0; // exact but for a sphere's empty tiles
     for (int r = 0; r < n; ++r) most += xy_tiles(reps[r], t) * ((reps[r].Lz + t.zc - 1) / t.zc);
     work.reserve(most);
     for (int r = 0; r < n; ++r) {
@@ -391,6 +391,22 @@ void make_work(const mc_replica_desc *reps, int n, const Tile &t, std::vector<Wo
                 }
         end[r] = (uint32_t)work.size();
     }
+}
+
+// Length of the work list.
+uint64_t count_work(const mc_replica_desc *reps, int n, const Tile &t)
+{
+    uint64_t items = 0;
+    bool cut = false;
+    for (int r = 0; r < n; ++r) {
+        items += xy_tiles(reps[r], t) * ((reps[r].Lz + t.zc - 1) / t.zc);
+        cut |= reps[r].sphere_radius > 0.0;
+    }
+    if (!cut) return items; // every tile is in the list
+    std::vector<WorkItem> work;
+    std::vector<uint32_t> b, e;
+    make_work(reps, n, t, work, b, e);
+    return work.size();
 }
 
 ScratchLayout scratch_layout(int n_reps, uint64_t n_items, int n_colours)
@@ -603,6 +619,33 @@ mc_status enqueue_sweeps(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bo
     return MC_OK;
 }
 
+// The current device's part of the autotuner's cache key, looked up once per
+// device ("" if it cannot be).
+std::string device_tune_key()
+{
+    static std::mutex mu;
+    static std::string known[64];
+    int dev = 0, n_xcd = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
+        (void)hipGetLastError();
+        return "";
+    }
+    std::lock_guard<std::mutex> lock(mu);
+    if (!known[dev].empty()) return known[dev];
+    hipDeviceProp_t prop;
+    std::memset(&prop, 0, sizeof prop);
+    if (hipGetDeviceProperties(&prop, dev) == hipSuccess) {
+        if (hipDeviceGetAttribute(&n_xcd, hipDeviceAttributeNumberOfXccs, dev) != hipSuccess)
+            n_xcd = 0;
+        char key[160];
+        if (mc_tune_device_key(prop.gcnArchName, prop.multiProcessorCount, n_xcd, key,
+                               sizeof key) == MC_OK)
+            known[dev] = key;
+    }
+    (void)hipGetLastError();
+    return known[dev];
+}
+
 // Whether the device deals workgroups to its eight XCDs in turn (workgroup b
 // on XCD b mod 8), checked once per device with a 64-workgroup launch that
 // records each workgroup's XCD.  `buf` holds at least 64 words.
@@ -636,8 +679,8 @@ bool device_deals_xcds(mc_sim *h, uint32_t *buf)
 }
 
 // Deal the replicas to the persistent-launch queues (see
-// mc_set_persistent_mode) and upload the queue table.  Asynchronous on the
-// handle's stream; h->q_host stays alive until the next call.
+// mc_set_persistent_mode) and, for more than one queue, upload the queue table.
+// Asynchronous on the handle's stream; h->q_host stays alive until the next call.
 mc_status plan_queues(mc_sim *h)
 {
     const int n = h->n_reps;
@@ -666,6 +709,7 @@ mc_status plan_queues(mc_sim *h)
         xcd = h->xcd_ok && n >= 8 && 8 * max_load * 4 <= sum * 5; // max <= 1.25 x mean
     h->n_queues = xcd ? 8 : 1;
     h->max_queue_items = xcd ? (uint32_t)max_load : (uint32_t)sum;
+    if (h->n_queues == 1) return MC_OK; // one queue is the work list itself
     h->q_host.assign(16 + h->work.size(), 0u);
     uint32_t pos = 0;
     for (int g = 0; g < 8; ++g) {
@@ -832,14 +876,18 @@ mc_status check_measure_args(const mc_replica_desc *d, mc_precision prec,
     return check_device_buffer(record_dev, sizeof(double) * NR, "record", 0);
 }
 
-mc_status upload_reps(mc_sim *h)
+mc_status send_reps(mc_sim *h) // asynchronous, from h->reps
 {
-    {
-        mc_status s = xchg_pull(h);
-        if (s != MC_OK) return s;
-    }
     HIP_TRY(hipMemcpyAsync(h->reps_dev, h->reps.data(), sizeof(RepDev) * h->n_reps,
                            hipMemcpyHostToDevice, h->stream));
+    return MC_OK;
+}
+
+mc_status upload_reps(mc_sim *h)
+{
+    mc_status s = xchg_pull(h);
+    if (s == MC_OK) s = send_reps(h);
+    if (s != MC_OK) return s;
     HIP_TRY(hipStreamSynchronize(h->stream));
     return MC_OK;
 }
@@ -977,10 +1025,8 @@ mc_status mc_required_scratch(const mc_replica_desc *reps, int32_t n_reps, uint6
     uint64_t need = 0;
     for (size_t esz : {sizeof(float), sizeof(double)}) {
         const Tile t = default_tile(reps, n_reps, esz);
-        std::vector<WorkItem> work;
-        std::vector<uint32_t> b, e;
-        make_work(reps, n_reps, t, work, b, e);
-        need = std::max(need, scratch_layout(n_reps, work.size(), n_colours_of(reps[0].kind)).total);
+        need = std::max(need, scratch_layout(n_reps, count_work(reps, n_reps, t),
+                                             n_colours_of(reps[0].kind)).total);
     }
     *bytes = need;
     return MC_OK;
@@ -1084,7 +1130,7 @@ mc_status mc_init_lattice(const mc_replica_desc *reps, int32_t n_reps, mc_precis
     h->xcd_ok = device_deals_xcds(h, h->queues_dev);
     mc_status s;
     if ((s = plan_queues(h)) != MC_OK) return cleanup(s);
-    if ((s = upload_reps(h)) != MC_OK) return cleanup(s);
+    if ((s = send_reps(h)) != MC_OK) return cleanup(s);
     if (hipMemcpyAsync(h->work_dev, h->work.data(), sizeof(WorkItem) * h->work.size(),
                        hipMemcpyHostToDevice, h->stream) != hipSuccess ||
         launch_set_counter(h->tctr, 0u, h->stream) != hipSuccess ||
@@ -1100,23 +1146,10 @@ mc_status mc_init_lattice(const mc_replica_desc *reps, int32_t n_reps, mc_precis
                 return cleanup(fail(MC_E_DEVICE, "init launch: %s", hipGetErrorString(er)));
         }
     }
-    if (hipStreamSynchronize(h->stream) != hipSuccess)
-        return cleanup(fail(MC_E_DEVICE, "init: %s", hipGetErrorString(hipGetLastError())));
     // the device as the autotuner's cache sees it (architecture, compute
     // units, XCDs: a partition mode changes the last two)
     {
-        int dev = 0, n_xcd = 0;
-        hipDeviceProp_t prop;
-        std::memset(&prop, 0, sizeof prop);
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) {
-            if (hipDeviceGetAttribute(&n_xcd, hipDeviceAttributeNumberOfXccs, dev) != hipSuccess)
-                n_xcd = 0;
-            char key[160];
-            if (mc_tune_device_key(prop.gcnArchName, prop.multiProcessorCount, n_xcd, key,
-                                   sizeof key) == MC_OK)
-                h->device_key = key;
-        }
-        (void)hipGetLastError();
+        h->device_key = device_tune_key();
         if (h->device_key.empty()) h->device_key = "unknown-device";
     }
     // lattices whose state fits one workgroup's LDS run whole sweeps there
@@ -1134,6 +1167,8 @@ mc_status mc_init_lattice(const mc_replica_desc *reps, int32_t n_reps, mc_precis
     }
     h->default_tile = h->tile;
     team_init(h);
+    if (hipStreamSynchronize(h->stream) != hipSuccess)
+        return cleanup(fail(MC_E_DEVICE, "init: %s", hipGetErrorString(hipGetLastError())));
     *out = h;
     return MC_OK;
 }

@@ -102,6 +102,9 @@ struct mc_sim {
     Tile default_tile{};         // the tile chosen by mc_init_lattice
     bool team_on = false;        // sweeps of the default tile run by teams
     char *team_ws = nullptr;     // device memory, null: no team for these lattices
+    bool team_owned = false;     // team_ws is the library's (else the scratch's spare end)
+    std::vector<mc::TeamWg> team_table; // as uploaded to team_wgs
+    uint64_t team_clear = 0;     // bytes of team_ws that start as zero
     mc::TeamWg *team_wgs = nullptr;
     uint64_t *team_words = nullptr;
     double *team_partials = nullptr;
@@ -125,11 +128,16 @@ uint32_t measure_blocks(const RepDev &R);
 mc_status check_measure_args(const mc_replica_desc *d, mc_precision prec,
                              const mc_spin_buffers *bufs, const double *record_dev);
 bool lds_fits(const mc_sim *h);
-// Team sweeps (abi_team.cpp): plan the teams of a new handle and allocate
-// their workspace, where the lattices are small enough to gain from them
+mc_status check_device_buffer(const void *p, uint64_t bytes, const char *what, int rep);
+// Team sweeps (abi_team.cpp): plan the teams of a new handle and find them a
+// workspace (the end of the scratch if it has room, else device memory of the
+// library's), where the lattices are small enough to gain from them
 // (leaves team_ws null otherwise); release it; enqueue n sweeps.
 void team_init(mc_sim *h);
 void team_release(mc_sim *h);
+// (Re)start the workspace's tags and table on the handle's stream and let the
+// teams run the default tile (a tile change may have used the scratch's end).
+hipError_t team_activate(mc_sim *h);
 // Records of a measured team launch in pinned memory besides the device ring:
 // none, the last sweep's (host_last), or all at their ring slots (host_rec).
 enum class TeamHost { none, last, all };

@@ -156,7 +156,15 @@ void team_init(mc_sim *h)
     const uint64_t off_words = (o = align_up(o + sizeof(TeamWg) * P.wgs.size(), 256));
     const uint64_t off_part = (o = align_up(o + sizeof(uint64_t) * P.words, 256));
     o += sizeof(double) * NQ * kTeamChunk * P.wgs.size();
-    if (hipMalloc((void **)&h->team_ws, o) != hipSuccess) {
+    const uint64_t spare = align_up(h->lay.total, 256);
+    h->team_owned = spare + o > h->scratch_bytes;
+    if (!h->team_owned && check_device_buffer(h->scratch, spare + o, "scratch", -1) != MC_OK) {
+        g_err.clear(); // the allocation ends before scratch_bytes: leave its end alone
+        h->team_owned = true;
+    }
+    if (!h->team_owned) {
+        h->team_ws = h->scratch + spare;
+    } else if (hipMalloc((void **)&h->team_ws, o) != hipSuccess) {
         (void)hipGetLastError();
         h->team_ws = nullptr;
         return;
@@ -168,22 +176,28 @@ void team_init(mc_sim *h)
     h->team_grid = (uint32_t)P.wgs.size();
     h->team_threads = P.threads;
     h->team_lds = P.lds;
-    // tags start above the zeroed words
-    const uint64_t words32 = off_part / sizeof(uint32_t);
-    if (launch_zero_u32(h->team_state, (uint32_t)words32, h->stream) != hipSuccess ||
-        hipMemcpyAsync(h->team_wgs, P.wgs.data(), sizeof(TeamWg) * P.wgs.size(),
-                       hipMemcpyHostToDevice, h->stream) != hipSuccess ||
-        hipStreamSynchronize(h->stream) != hipSuccess) {
+    h->team_clear = off_part;
+    h->team_table.swap(P.wgs);
+    if (team_activate(h) != hipSuccess) {
         (void)hipGetLastError();
         team_release(h);
-        return;
     }
+}
+
+hipError_t team_activate(mc_sim *h)
+{
+    // tags start above the zeroed words
+    const hipError_t e =
+        launch_zero_u32(h->team_state, (uint32_t)(h->team_clear / sizeof(uint32_t)), h->stream);
+    if (e != hipSuccess) return e;
     h->team_on = true;
+    return hipMemcpyAsync(h->team_wgs, h->team_table.data(), sizeof(TeamWg) * h->team_table.size(),
+                          hipMemcpyHostToDevice, h->stream);
 }
 
 void team_release(mc_sim *h)
 {
-    if (h->team_ws) (void)hipFree(h->team_ws);
+    if (h->team_ws && h->team_owned) (void)hipFree(h->team_ws);
     h->team_ws = nullptr;
     h->team_on = false;
 }

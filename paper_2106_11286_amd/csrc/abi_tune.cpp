@@ -108,8 +108,10 @@ mc_status choose_tile(mc_sim *h, const Tile &t, bool teams)
 {
     const Tile d = t.kernel == TEAM_CANDIDATE ? h->default_tile : t;
     const mc_status st = mc_set_tile(h, d.kernel, d.tx, d.ty, d.zc);
-    if (st == MC_OK) h->team_on = teams && h->team_ws;
-    return st;
+    if (st != MC_OK || !teams || !h->team_ws) return st;
+    HIP_TRY(team_activate(h));
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    return MC_OK;
 }
 
 bool same_tile(const Tile &a, const Tile &b)

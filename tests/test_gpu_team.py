@@ -70,6 +70,34 @@ def test_team_sweeps_are_bitwise(M, name):
     assert [o["n_sites"] for o in st] == a.n_occ
 
 
+@pytest.mark.parametrize("spare", [0, 1 << 20, 16 << 20])
+def test_team_workspace(M, spare):
+    """The workspace at the end of the caller's scratch, or the library's own
+    where the scratch has no room; it starts over after a tile change."""
+    import torch
+
+    reps = [M.Replica(kind="sc", L=(24, 24, 24), K=0.1, T=1.0 + 0.1 * r, replica_id=r)
+            for r in range(5)]
+    scratch = torch.full((M.required_scratch(reps) + spare,), 255, dtype=torch.uint8, device="cuda")
+    a = M.Simulation(reps, precision="f32", seed=9, scratch=scratch)
+    b = M.Simulation(reps, precision="f32", seed=9)
+    b.set_tile(256, 2, 2, kernel=2)
+    for s in (a, b):
+        s.sweep(5, measure=True)
+    _same_spins(a, b)
+    _same_obs(a.observables(), b.observables())
+    a.set_tile(64, 2, 1, kernel=1) if spare else a.set_tile(256, 2, 4, kernel=2)
+    for s in (a, b):
+        s.sweep(3, measure=True)
+    _same_spins(a, b)
+    t = a.get_sweep()
+    a.autotune(trial_sweeps=1, measure=True)
+    a.sweep(2, measure=True)
+    b.sweep(a.get_sweep() - t, measure=True)
+    _same_spins(a, b)
+    _same_obs(a.observables(), b.observables())
+
+
 def test_team_records_and_replays(M):
     """More measured sweeps than one launch takes, schedules replayed as
     graphs with eager sweeps between the replays, and a resumed counter."""
