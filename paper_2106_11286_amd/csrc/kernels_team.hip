@@ -126,24 +126,51 @@ __global__ void __launch_bounds__(TEAM_THREADS, sizeof(T) == 8 ? 2 : 4) k_team_s
     // the owned planes and the halo planes as they are before the launch
     // (a neighbour writes its planes back only after its last phase, which
     // needs words published after this load)
+    // several elements' loads are in flight at a time
+    auto fill = [&](uint32_t n, auto source) __attribute__((always_inline)) {
+        constexpr int U = 4;
+        for (uint32_t i0 = tid; i0 < n; i0 += U * nt) {
+            Vec3<T> v[U];
+            uint32_t dst[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t i = i0 + (uint32_t)u * nt;
+                uint32_t g = 0;
+                const bool there = i < n && source(i, g, dst[u]);
+                v[u] = {T(0), T(0), T(0)};
+                if (there) v[u] = {gx[g], gy[g], gz[g]};
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i0 + (uint32_t)u * nt < n) {
+                    lx[dst[u]] = v[u].x;
+                    ly[dst[u]] = v[u].y;
+                    lz[dst[u]] = v[u].z;
+                }
+        }
+    };
     for (int c = 0; c < NC; ++c) {
         const uint32_t gsrc = (uint32_t)c * plane, ldst = (uint32_t)c * lplane;
-        for (uint32_t i = tid; i < own; i += nt) {
-            const uint32_t g = gsrc + (uint32_t)w.z0 * psites + i, l = ldst + psites + i;
-            lx[l] = gx[g];
-            ly[l] = gy[g];
-            lz[l] = gz[g];
-        }
-        for (uint32_t i = tid; i < 2 * psites; i += nt) {
+        fill(own, [&](uint32_t i, uint32_t &g, uint32_t &l) {
+            g = gsrc + (uint32_t)w.z0 * psites + i;
+            l = ldst + psites + i;
+            return true;
+        });
+        if (c == 0) continue; // colour 0 is updated before its halo is first read
+        fill(2 * psites, [&](uint32_t i, uint32_t &g, uint32_t &l) {
             const bool up = i >= psites;
             const uint32_t k = up ? i - psites : i;
             const int z = up ? w.z_hi : w.z_lo;
-            const uint32_t l = ldst + (up ? (uint32_t)(nz + 1) * psites : 0u) + k;
-            const uint32_t g = gsrc + (uint32_t)(z < 0 ? 0 : z) * psites + k;
-            lx[l] = z < 0 ? T(0) : gx[g];
-            ly[l] = z < 0 ? T(0) : gy[g];
-            lz[l] = z < 0 ? T(0) : gz[g];
-        }
+            l = ldst + (up ? (uint32_t)(nz + 1) * psites : 0u) + k;
+            g = gsrc + (uint32_t)(z < 0 ? 0 : z) * psites + k;
+            return z >= 0;
+        });
+    }
+    // beyond an open face colour 0 reads as zero, too
+    for (uint32_t i = tid; i < psites; i += nt) {
+        if (w.z_lo < 0) lx[i] = ly[i] = lz[i] = T(0);
+        const uint32_t l = (uint32_t)(nz + 1) * psites + i;
+        if (w.z_hi < 0) lx[l] = ly[l] = lz[l] = T(0);
     }
     uint64_t *const words = L.words + w.words;
     const uint32_t slot_words = (uint32_t)(NC * NW) * psites;
@@ -352,14 +379,6 @@ __global__ void __launch_bounds__(TEAM_THREADS, sizeof(T) == 8 ? 2 : 4) k_team_s
         __hip_atomic_store(L.host_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     __syncthreads();
-    for (int c = 0; c < NC; ++c)
-        for (uint32_t i = tid; i < own; i += nt) {
-            const uint32_t g = (uint32_t)c * plane + (uint32_t)w.z0 * psites + i;
-            const uint32_t l = (uint32_t)c * lplane + psites + i;
-            gx[g] = lx[l];
-            gy[g] = ly[l];
-            gz[g] = lz[l];
-        }
     // The last workgroup of a replica to get here turns its team's sums into
     // records; the last of the launch advances the counters, which every
     // workgroup has read by then.  The sums were stored by agent-scope
@@ -373,6 +392,14 @@ __global__ void __launch_bounds__(TEAM_THREADS, sizeof(T) == 8 ? 2 : 4) k_team_s
         if (s_last)
             __hip_atomic_store(L.done + 1u + w.rep, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    for (int c = 0; c < NC; ++c)
+        for (uint32_t i = tid; i < own; i += nt) {
+            const uint32_t g = (uint32_t)c * plane + (uint32_t)w.z0 * psites + i;
+            const uint32_t l = (uint32_t)c * lplane + psites + i;
+            gx[g] = lx[l];
+            gy[g] = ly[l];
+            gz[g] = lz[l];
+        }
     __syncthreads();
     if (MEASURE && s_last) {
         for (uint32_t j = tid; j < L.n_sweeps * 8u; j += nt) {
