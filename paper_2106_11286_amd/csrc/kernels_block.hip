@@ -133,15 +133,35 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_block_apply(BlockLaunch B)
 {
     if (blockIdx.x + 1u == gridDim.x) {
-        // the last workgroup adds the step's counts to the totals: wave q sums
-        // count q over the slots
-        const uint32_t q = threadIdx.x >> 6;
-        if (q >= 3u) return;
-        unsigned long long v = 0;
-        for (uint32_t j = threadIdx.x & 63u; j < B.n_slots; j += 64u) v += B.slots[j * 4u + q];
+        // the last workgroup adds the step's counts to the totals: every
+        // thread takes its slots' three counts, all loads in flight at once
+        __shared__ uint32_t s_sum[4][3];
+        constexpr uint32_t PER = BLOCK_SLOTS / 256u;
+        uint4 c[PER];
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-        if ((threadIdx.x & 63u) == 0) B.counts[q] += v;
+        for (uint32_t u = 0; u < PER; ++u) {
+            const uint32_t j = threadIdx.x + u * 256u;
+            c[u] = j < B.n_slots ? ((const uint4 *)B.slots)[j] : make_uint4(0, 0, 0, 0);
+        }
+        uint32_t v[3] = {0, 0, 0};
+#pragma unroll
+        for (uint32_t u = 0; u < PER; ++u) {
+            v[0] += c[u].x;
+            v[1] += c[u].y;
+            v[2] += c[u].z;
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) v[q] += __shfl_xor(v[q], o, 64);
+        if ((threadIdx.x & 63u) == 0)
+            for (int q = 0; q < 3; ++q) s_sum[threadIdx.x >> 6][q] = v[q];
+        __syncthreads();
+        if (threadIdx.x < 3u) {
+            unsigned long long n = 0;
+            for (int w = 0; w < 4; ++w) n += s_sum[w][threadIdx.x];
+            B.counts[threadIdx.x] += n;
+        }
         return;
     }
     const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
