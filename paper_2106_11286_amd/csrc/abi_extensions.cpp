@@ -26,13 +26,9 @@ XchgPtrs xchg_ptrs(const mc_sim *h)
             (uint32_t *)(b + 24 * n), (uint32_t *)(b + 28 * n)};
 }
 
-mc_status xchg_pull(mc_sim *h)
+// The host descriptors' temperatures from the device's slot table.
+mc_status xchg_take(mc_sim *h, const uint32_t *rep_at)
 {
-    if (!h->xchg_active) return MC_OK;
-    std::vector<uint32_t> rep_at(h->n_reps);
-    HIP_TRY(hipStreamSynchronize(h->stream));
-    HIP_TRY(hipMemcpy(rep_at.data(), xchg_ptrs(h).rep_at, sizeof(uint32_t) * h->n_reps,
-                      hipMemcpyDeviceToHost));
     for (int k = 0; k < h->n_reps; ++k) {
         const uint32_t r = rep_at[k];
         if (r >= (uint32_t)h->n_reps) return fail(MC_E_DEVICE, "exchange table corrupted");
@@ -40,6 +36,16 @@ mc_status xchg_pull(mc_sim *h)
         set_temperature(h->reps[r], h->xchg_T[k]);
     }
     return MC_OK;
+}
+
+mc_status xchg_pull(mc_sim *h)
+{
+    if (!h->xchg_active) return MC_OK;
+    std::vector<uint32_t> rep_at(h->n_reps);
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    HIP_TRY(hipMemcpy(rep_at.data(), xchg_ptrs(h).rep_at, sizeof(uint32_t) * h->n_reps,
+                      hipMemcpyDeviceToHost));
+    return xchg_take(h, rep_at.data());
 }
 
 // Identical lattices and couplings (all but T and replica_id).
@@ -135,18 +141,16 @@ mc_status mc_exchange_state(mc_sim *h, int32_t *replica_at_slot, double *T_slot,
 {
     if (!alive(h)) return fail(MC_E_STATE, "invalid or destroyed handle");
     if (!h->xchg_active) return fail(MC_E_STATE, "replica exchange not initialised (mc_exchange_init)");
+    // the table in one copy (beta, attempted, accepted, rep_at, round)
+    const int n = h->n_reps;
+    char *const t = (char *)h->host_rec;
+    HIP_TRY(hipMemcpyAsync(t, h->scratch + h->lay.off_exchange, 28 * (size_t)n + 4,
+                           hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     mc_status st = check_persistent(h);
     if (st != MC_OK) return st;
-    const int n = h->n_reps;
-    const XchgPtrs x = xchg_ptrs(h);
-    std::vector<uint32_t> rep_at(n);
-    std::vector<uint64_t> att(n), acc(n);
-    uint32_t rnd = 0;
-    HIP_TRY(hipMemcpy(rep_at.data(), x.rep_at, sizeof(uint32_t) * n, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(att.data(), x.attempted, sizeof(uint64_t) * n, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(acc.data(), x.accepted, sizeof(uint64_t) * n, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(&rnd, x.round, sizeof rnd, hipMemcpyDeviceToHost));
+    const uint64_t *att = (const uint64_t *)(t + 8 * (size_t)n), *acc = att + n;
+    const uint32_t *rep_at = (const uint32_t *)(t + 24 * (size_t)n);
     for (int k = 0; k < n; ++k) {
         if (replica_at_slot) replica_at_slot[k] = (int32_t)rep_at[k];
         if (T_slot) T_slot[k] = h->xchg_T[k];
@@ -155,8 +159,8 @@ mc_status mc_exchange_state(mc_sim *h, int32_t *replica_at_slot, double *T_slot,
             if (accepted) accepted[k] = acc[k];
         }
     }
-    if (rounds) *rounds = rnd;
-    return xchg_pull(h);
+    if (rounds) *rounds = rep_at[n];
+    return xchg_take(h, rep_at);
 }
 
 mc_status mc_block_workspace(const mc_sim *h, uint32_t n, uint64_t *bytes)
