@@ -27,7 +27,8 @@ namespace mc {
 // phase p + NC: by then its owner has seen words of phase p or later from
 // every reader, which published them after the workgroup barrier that ended
 // its own reads of phase p.  Proposals do not depend on the spins and are
-// drawn between the request for the words and their arrival.
+// drawn between the request for the words and their arrival (FP64: ahead of the
+// request).
 //
 // The site updates are the other kernels' templates on the same values in the
 // same order (a missing plane beyond an open face reads as zero, which adds
@@ -240,9 +241,16 @@ __global__ void __launch_bounds__(TEAM_THREADS, sizeof(T) == 8 ? 2 : 4) k_team_s
                 ly[l] = v.y;
                 lz[l] = v.z;
             };
-            // request this thread's first halo words, draw its first site's
-            // proposal meanwhile, then wait for the words
-            if (mine) request(tid);
+            // Request this thread's first halo words, draw its first site's
+            // proposal meanwhile, then wait for the words.  An FP64 proposal
+            // takes longer than the neighbours need: words asked for before it
+            // come back old and are asked for again, so FP64 asks after it.
+            // us per sweep, before / after: FP32 24^3 x 17 7.12 / 7.88,
+            // 50x37x23 8.22 / 8.50; FP64 16^3 4.87 / 4.61, 20^3 x 3 5.34 / 4.97,
+            // fcc 16^3 13.3 / 12.8.
+            constexpr bool ask_first = sizeof(T) == 4;
+            if constexpr (ask_first)
+                if (mine) request(tid);
             uint32_t k = tid;
             bool first = true;
 #pragma clang loop unroll(disable)
@@ -256,6 +264,7 @@ __global__ void __launch_bounds__(TEAM_THREADS, sizeof(T) == 8 ? 2 : 4) k_team_s
                 if (first) {
                     first = false;
                     if (mine) {
+                        if constexpr (!ask_first) request(tid);
 #pragma clang loop unroll(disable)
                         for (uint32_t i = tid;;) {
                             for (uint32_t spins = 1;
