@@ -512,7 +512,12 @@ __device__ __forceinline__ void buf_store2(double a, double b, rsrc_t r, uint32_
     v.y = (uint32_t)__double2hiint(a);
     v.z = (uint32_t)__double2loint(b);
     v.w = (uint32_t)__double2hiint(b);
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, 0);
+    // The scalar offset goes into the lane offset: a store of more than 8 bytes
+    // whose data registers are overwritten within two wait states stores the
+    // new values, and the compiler keeps that distance only for stores without
+    // a scalar offset register (seen on sc 464^3: the low column's x component
+    // of some rows held the next selection's result).
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, voff + soff, 0, 0);
 }
 
 // Field at basis site B of cell (x, y, z) (J not applied): hx.. over all
