@@ -550,6 +550,8 @@ class Simulation:
         for i, (pl, n) in enumerate(zip(alt, self.sites)):
             bufs[i].sx, bufs[i].sy, bufs[i].sz = pl[0].data_ptr(), pl[1].data_ptr(), pl[2].data_ptr()
             bufs[i].capacity_sites = n
+        # the zeros are written on torch's stream, the sweeps run on another
+        torch.cuda.synchronize(self.device)
         _check("mc_set_second_buffers", LIB.mc_set_second_buffers(self.handle, bufs))
         self.alt_spins = alt
 
