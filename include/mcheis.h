@@ -165,7 +165,9 @@ mc_status mc_required_scratch(const mc_replica_desc *reps, int32_t n_reps, uint6
  * each spin uniformly on the sphere, the aligned start sets S = e.
  *  bufs[n_reps]  spin planes per replica (device memory);
  *  scratch       device memory of at least mc_required_scratch bytes, 256-byte
- *                aligned, owned by the caller, used only by this handle;
+ *                aligned, owned by the caller, used only by this handle (small
+ *                lattices keep a few MB of team-sweep state in its spare end;
+ *                the library allocates that itself where there is no room);
  *  hip_stream    hipStream_t every call enqueues on (NULL = default stream).
  * Random start: spin s = sphere(Philox(seed, (s, replica_id, 0, 1))).
  * Errors: MC_E_ARG (n_reps < 1, lengths < 1, T < 0 or NaN, |e| = 0, mixed
@@ -285,19 +287,25 @@ mc_status mc_set_sweep(mc_sim *h, uint64_t t);
  *  kernel 1 (sc only): tx threads along the row (64, 128, 192 or 256), each
  *    holding ty consecutive rows (1, 2, 4 or 8), with the other colour kept in
  *    registers across planes;
- *  kernel 2 (sc only; the default for short or odd rows): as kernel 1, but
+ *  kernel 2 (sc only; the default for short or odd rows, and for rows that
+ *    leave more than a fifth of kernel 4's lanes idle): as kernel 1, but
  *    rows grouped in bands of ty rows (2 or 4) and the (band, column)
  *    positions dealt to the tx threads contiguously, so no lane idles
  *    whatever the row length; a tile is tx positions x zc planes;
  *  kernel 3 (any lattice whose three component planes fit one workgroup's
  *    LDS; the default then): whole sweeps in LDS, one workgroup of tx threads
  *    (64 .. 1024, multiple of 64) per replica, colour passes separated by
- *    workgroup barriers; ty and zc are ignored.  Single passes (mc_debug_pass,
- *    mc_measure_state) keep using the previous pass kernel.  A replica too
- *    large gives MC_E_UNSUPPORTED;
+ *    workgroup barriers; ty and zc are ignored.  On the default tile, also of
+ *    other lattices of up to 400,000 box sites in all, a team of workgroups
+ *    per replica runs the sweeps instead where that is faster: each holds a
+ *    share of the planes in LDS and exchanges its boundary planes with its
+ *    neighbours after every colour; choosing a tile ends it (the chain is the
+ *    same).  Single passes (mc_debug_pass, mc_measure_state) keep using the
+ *    previous pass kernel.  A replica too large gives MC_E_UNSUPPORTED;
  *  kernel 4 (sc only, every row of an even number of packed columns; the
- *    default when every row also has at least 96 packed columns): as
- *    kernel 1 with two adjacent columns per thread, read and written as one
+ *    default when every row also has at least 96 packed columns and four
+ *    fifths of the lanes hold a pair): as kernel 1 with two adjacent columns
+ *    per thread, read and written as one
  *    8-byte (FP32) or 16-byte (FP64) access; tx threads (64 .. 256) cover 2 tx
  *    columns, ty rows per thread (1, 2 or 4; persistent sweeps: 1 or 2);
  *  kernel 5 (sc only, even packed rows): as kernel 2 with two adjacent

@@ -6,8 +6,9 @@
 // abi_tune.cpp, abi_stats.cpp and abi_extensions.cpp.
 //
 // The library allocates no spin or scratch memory: the caller owns both (in
-// practice as framework tensors) and the stream.  The only allocation it makes
-// is a small pinned host ring for observable records.
+// practice as framework tensors) and the stream.  What it allocates is a small
+// pinned host ring for observable records and, where the scratch has no room
+// left for it, the state of team sweeps (a few MB).
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
