@@ -311,10 +311,11 @@ mc_status mc_set_sweep(mc_sim *h, uint64_t t);
  *  kernel 5 (sc only, even packed rows): as kernel 2 with two adjacent
  *    columns per thread: tx (64 .. 256) (band, pair) positions per workgroup,
  *    bands of ty rows (2 or 4; FP64 and persistent sweeps: 2);
- *  kernel 6 (bcc and fcc): tx lanes along x (64, 128, 192 or 256) times ty
- *    rows (tx*ty <= 256), zc planes walked in z with the other basis sites'
- *    planes kept in registers and the x neighbour taken from the adjacent
- *    lane (persistent sweeps run the kernel-0 body on the same tile);
+ *  kernel 6 (bcc and fcc; the default for odd Lx from 33 cells per row on, up
+ *    to 4 GiB per spin component array): tx lanes along x (64, 128, 192 or
+ *    256) times ty rows (tx*ty <= 256), zc planes walked in z with the other
+ *    basis sites' planes kept in registers and the x neighbour taken from the
+ *    adjacent lane (persistent sweeps run the kernel-0 body on the same tile);
  *  kernel 7 (bcc and fcc, every replica with Lx even; the default then, up
  *    to 4 GiB per spin component array): two adjacent cells of one basis per
  *    thread (one 8-byte FP32 / 16-byte FP64 access per component), bands of

@@ -140,7 +140,12 @@ uint64_t xy_tiles(const mc_replica_desc &d, const Tile &t)
 //    35.9 / 43.0; bcc 128^3 zc 1 35.1 / 43.5, zc 4 30.4 / 37.6;
 //  * a larger one with about 6000 workgroups (FP64 3500): 302 x 251 x 210 zc 2
 //    104 / 120, zc 3 104 / 113, zc 5 115 / 119; 464^3 zc 14 803 / 805, zc 8
-//    766 / 780; FP64 464^3 zc 5 1576 / 1611, zc 16 1570 / 1582, zc 24 1576 / 1589.
+//    766 / 780; FP64 464^3 zc 5 1576 / 1611, zc 16 1570 / 1582, zc 24 1576 / 1589;
+//  * the tile and basis strip kernels walk little or no state along z and want
+//    more workgroups (strip, bcc 33 x 80 x 80 zc 1 11.9 / 19.8, zc 2 13.0 / 20.0;
+//    111 x 120 x 90 zc 2 26.3 / 35.6, zc 6 32.2 / 39.1; 151 x 150 x 149 zc 4
+//    63.7 / 75.3, zc 8 73.5 / 80.8; tile, 111 x 120 x 90 zc 2 36.5 / 46.3, zc 6
+//    54.0 / 62.5; FP64 fcc 17 x 80 x 80 zc 1 36.1 / 45.0, zc 2 46.7 / 55.5).
 int z_chunk(const mc_replica_desc *reps, int n, const Tile &t, size_t esz)
 {
     uint64_t cols = 0, planes = 0;
@@ -155,11 +160,14 @@ int z_chunk(const mc_replica_desc *reps, int n, const Tile &t, size_t esz)
         zc = (cols + kTargetItems - 1) / kTargetItems;
     } else {
         const bool f64 = esz == sizeof(double);
-        const bool flat = t.kernel == KERNEL_TILE; // tx * ty threads, else tx
+        // tx * ty threads, else tx
+        const bool flat = t.kernel == KERNEL_TILE || t.kernel == KERNEL_BSTRIP;
         const uint64_t threads = (uint64_t)t.tx * (uint64_t)(flat ? t.ty : 1);
         const uint64_t p = std::max<uint64_t>(1, cols * threads / 256);
         // fcc FP32 holds fewer registers: 128^3 zc 4 90 / 100, zc 2 86 / 95
-        const uint64_t round = f64 ? 512 : reps[0].kind == MC_FCC ? 2048 : 1024;
+        const uint64_t round = flat  ? (f64 ? 1400 : 4000)
+                               : f64 ? 512
+                                     : reps[0].kind == MC_FCC ? 2048 : 1024;
         const uint64_t many = f64 ? 3500 : 6000;
         zc = (p + round - 1) / round;
         if (zc > 8) zc = (p + many / 2) / many;
@@ -242,6 +250,16 @@ Tile default_tile(const mc_replica_desc *reps, int n, size_t esz)
         t.kernel = KERNEL_BPAIR;
         t.tx = cut ? 64 : 256;
         t.ty = reps[0].kind == MC_FCC || esz == sizeof(double) || bytes <= 256000000ull ? 1 : 2;
+    } else if (reps[0].kind != MC_SC && fits && Wmin > 32) {
+        // rows of an odd number of cells that fill more than half of a wave:
+        // one row per wave (tile 64 x 4 / strip, us per sweep: bcc 55 x 66 x 92
+        // 14.9 / 22.4 -> 12.3 / 20.1, 111 x 120 x 90 34.6 / 47.2 -> 26.3 / 35.6,
+        // 201 x 200 x 199 208 / 253 -> 131 / 147, fcc 33 x 64 x 64 25.9 / 34.3 ->
+        // 21.1 / 29.5).  Shorter rows leave its lanes idle (bcc 9 x 100 x 100:
+        // tile 11.5 / 18.4, strip 14.4 / 23.0; FP64 fcc 17 x 80 x 80 36 / 45, 51 / 61).
+        t.kernel = KERNEL_BSTRIP;
+        t.tx = 64;
+        t.ty = 4;
     } else {
         t.kernel = KERNEL_TILE;
         t.tx = std::min(64, pow2_at_least(W));
