@@ -8,8 +8,8 @@
 // lattice through the L2 per step.  Each XCD takes a contiguous eighth of the
 // blocks, so its part of the lattice stays in its L2; the counts go to one
 // slot per workgroup and are summed by one workgroup of the second launch
-// (three same-address atomics per wave, 12.6 ns each in turn, took 155 us a
-// step at 128^3, n = 8, against 10 now); the divisions by the
+// (three same-address atomics per wave, 12.6 ns each in turn, made a step of
+// 128^3, n = 8, 163 us; it takes 22 now); the divisions by the
 // lattice edges and by n are multiplications by host-made constants.
 #include "device_common.hpp"
 
