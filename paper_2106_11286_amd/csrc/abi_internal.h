@@ -104,7 +104,9 @@ struct mc_sim {
     char *team_ws = nullptr;     // device memory, null: no team for these lattices
     bool team_owned = false;     // team_ws is the library's (else the scratch's spare end)
     std::vector<mc::TeamWg> team_table; // as uploaded to team_wgs
-    uint64_t team_clear = 0;     // bytes of team_ws that start as zero
+    uint64_t team_off_wgs = 0, team_off_words = 0; // in team_ws, after the state words
+    uint64_t team_off_part = 0;  // partial sums; what lies before starts as zero
+    uint64_t team_bytes = 0;     // size of team_ws
     mc::TeamWg *team_wgs = nullptr;
     uint64_t *team_words = nullptr;
     double *team_partials = nullptr;
@@ -136,8 +138,16 @@ mc_status check_device_buffer(const void *p, uint64_t bytes, const char *what, i
 void team_init(mc_sim *h);
 void team_release(mc_sim *h);
 // (Re)start the workspace's tags and table on the handle's stream and let the
-// teams run the default tile (a tile change may have used the scratch's end).
+// teams run the default tile.  Where the layout in force has grown over the
+// workspace it moves to device memory of the library's; the teams stay off if
+// there is none.
 hipError_t team_activate(mc_sim *h);
+// Offset of a workspace of `need` bytes at the end of the scratch, clear of a
+// layout of `used` bytes, or kTeamNoRoom.
+constexpr uint64_t kTeamNoRoom = ~0ull;
+uint64_t team_offset(uint64_t scratch_bytes, uint64_t used, uint64_t need);
+// Whether the workspace lies outside the layout in force.
+bool team_disjoint(const mc_sim *h);
 // Records of a measured team launch in pinned memory besides the device ring:
 // none, the last sweep's (host_last), or all at their ring slots (host_rec).
 enum class TeamHost { none, last, all };

@@ -95,6 +95,28 @@ TeamPlan plan_teams(const mc_sim *h, uint32_t q)
     return P;
 }
 
+void team_bind(mc_sim *h, char *ws, bool owned)
+{
+    h->team_ws = ws;
+    h->team_owned = owned;
+    h->team_state = (uint32_t *)ws;
+    h->team_wgs = (TeamWg *)(ws + h->team_off_wgs);
+    h->team_words = (uint64_t *)(ws + h->team_off_words);
+    h->team_partials = (double *)(ws + h->team_off_part);
+}
+
+// A workspace of the library's own.
+bool team_own(mc_sim *h)
+{
+    char *ws = nullptr;
+    if (hipMalloc((void **)&ws, h->team_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    team_bind(h, ws, true);
+    return true;
+}
+
 } // namespace
 
 namespace mcabi {
@@ -152,43 +174,48 @@ void team_init(mc_sim *h)
     if (!found) return;
     uint64_t o = 0;
     const uint64_t n_state = 2 + 1 + (uint64_t)h->n_reps;
-    const uint64_t off_wgs = (o = align_up(sizeof(uint32_t) * n_state, 256));
-    const uint64_t off_words = (o = align_up(o + sizeof(TeamWg) * P.wgs.size(), 256));
-    const uint64_t off_part = (o = align_up(o + sizeof(uint64_t) * P.words, 256));
-    o += sizeof(double) * NQ * kTeamChunk * P.wgs.size();
-    const uint64_t spare = align_up(h->lay.total, 256);
-    h->team_owned = spare + o > h->scratch_bytes;
-    if (!h->team_owned && check_device_buffer(h->scratch, spare + o, "scratch", -1) != MC_OK) {
-        g_err.clear(); // the allocation ends before scratch_bytes: leave its end alone
-        h->team_owned = true;
-    }
-    if (!h->team_owned) {
-        h->team_ws = h->scratch + spare;
-    } else if (hipMalloc((void **)&h->team_ws, o) != hipSuccess) {
-        (void)hipGetLastError();
-        h->team_ws = nullptr;
-        return;
-    }
-    h->team_state = (uint32_t *)h->team_ws;
-    h->team_wgs = (TeamWg *)(h->team_ws + off_wgs);
-    h->team_words = (uint64_t *)(h->team_ws + off_words);
-    h->team_partials = (double *)(h->team_ws + off_part);
+    h->team_off_wgs = (o = align_up(sizeof(uint32_t) * n_state, 256));
+    h->team_off_words = (o = align_up(o + sizeof(TeamWg) * P.wgs.size(), 256));
+    h->team_off_part = (o = align_up(o + sizeof(uint64_t) * P.words, 256));
+    h->team_bytes = o + sizeof(double) * NQ * kTeamChunk * P.wgs.size();
     h->team_grid = (uint32_t)P.wgs.size();
     h->team_threads = P.threads;
     h->team_lds = P.lds;
-    h->team_clear = off_part;
     h->team_table.swap(P.wgs);
+    const uint64_t at = team_offset(h->scratch_bytes, h->lay.total, h->team_bytes);
+    if (at != kTeamNoRoom &&
+        check_device_buffer(h->scratch, at + h->team_bytes, "scratch", -1) == MC_OK) {
+        team_bind(h, h->scratch + at, false);
+    } else {
+        g_err.clear(); // the allocation ends before scratch_bytes: leave its end alone
+        if (!team_own(h)) return;
+    }
     if (team_activate(h) != hipSuccess) {
         (void)hipGetLastError();
         team_release(h);
     }
 }
 
+uint64_t team_offset(uint64_t scratch_bytes, uint64_t used, uint64_t need)
+{
+    if (need > scratch_bytes) return kTeamNoRoom;
+    const uint64_t at = (scratch_bytes - need) / 256 * 256;
+    return at >= used ? at : kTeamNoRoom;
+}
+
+bool team_disjoint(const mc_sim *h)
+{
+    return h->team_owned || h->lay.total <= (uint64_t)(h->team_ws - h->scratch);
+}
+
 hipError_t team_activate(mc_sim *h)
 {
+    // a tile chosen since may have taken the scratch up to its end, and the LDS
+    // kernel keeps the layout of the tile before it
+    if (!team_disjoint(h) && !team_own(h)) return hipSuccess; // the plain kernels go on
     // tags start above the zeroed words
     const hipError_t e =
-        launch_zero_u32(h->team_state, (uint32_t)(h->team_clear / sizeof(uint32_t)), h->stream);
+        launch_zero_u32(h->team_state, (uint32_t)(h->team_off_part / sizeof(uint32_t)), h->stream);
     if (e != hipSuccess) return e;
     h->team_on = true;
     return hipMemcpyAsync(h->team_wgs, h->team_table.data(), sizeof(TeamWg) * h->team_table.size(),
