@@ -408,12 +408,23 @@ mc_status mc_num_colours(const mc_sim *h, int32_t *n_colours);
 mc_status mc_series_stats(const mc_obs *series, uint64_t n, uint64_t stride, double T,
                           mc_stats *out);
 
+/* Team sweeps (see kernel 3 of mc_set_tile) of one replica: workgroups of its
+ * team (0 where the sweeps of the tile in force do not run by teams), planes of
+ * the team's first and of its last workgroup, and how many teams' launches of
+ * the handle were done again by one workgroup so far because a wait gave up.
+ * The out pointers may be NULL; with `redone` the call synchronises. */
+mc_status mc_get_team(mc_sim *h, int32_t replica, int32_t *workgroups, int32_t *planes,
+                      int32_t *last_planes, uint64_t *redone);
+
 /* Bounded wait of persistent launches: a work unit waiting for its replica's
  * previous pass gives up after `spins` polls (about 0.1 us each; default
  * 2^24).  A launch that gave up sets the handle's watchdog flag, which later
  * launches keep: the next synchronising call returns MC_E_DEVICE (and clears
  * the flag) and the spins of that call are incomplete.  Every workgroup still
- * exits normally.  Waits for the handle's enqueued work first. */
+ * exits normally.  The workgroups of a team (mc_get_team) give up after at most
+ * 2^16 polls (about 0.5 us each) or `spins` if that is less; nothing is lost
+ * then, one workgroup per replica does the launch's sweeps again, more slowly.
+ * Waits for the handle's enqueued work first. */
 mc_status mc_set_watchdog(mc_sim *h, uint32_t spins);
 
 /* Replica exchange (parallel tempering) between the handle's replicas, an

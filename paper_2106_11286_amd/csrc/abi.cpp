@@ -797,15 +797,10 @@ mc_status enqueue_persistent(mc_sim *h, uint32_t n, bool measure, uint32_t slot0
     return MC_OK;
 }
 
-// After a synchronisation: report a team or persistent launch whose bounded
-// wait gave up (the spins of that call are then incomplete).
+// After a synchronisation: report a persistent launch whose bounded wait gave
+// up (the spins of that call are then incomplete).
 mc_status check_persistent(mc_sim *h)
 {
-    if (*h->host_flag) {
-        *h->host_flag = 0;
-        return fail(MC_E_DEVICE, "team sweep: a wait for a neighbouring workgroup's planes gave "
-                                 "up; the state of that call is incomplete");
-    }
     if (!h->persist_used) return MC_OK;
     uint32_t hdr[2] = {0, 0};
     HIP_TRY(hipMemcpy(hdr, h->pstate, sizeof hdr, hipMemcpyDeviceToHost));
@@ -1138,16 +1133,14 @@ mc_status mc_init_lattice(const mc_replica_desc *reps, int32_t n_reps, mc_precis
         h->n_occ[r] = count_occupied(d);
         if (h->n_occ[r] == 0) return cleanup(fail(MC_E_ARG, "replica %d has no occupied site", r));
     }
-    // the ring with its measurement slot, the last sweep's records, a flag word
-    if (hipHostMalloc((void **)&h->host_rec, sizeof(double) * NR * (n_reps * (kRing + 2ull) + 1),
+    // the ring with its measurement slot, the last sweep's records
+    if (hipHostMalloc((void **)&h->host_rec, sizeof(double) * NR * n_reps * (kRing + 2ull),
                       hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         h->host_rec = nullptr;
         return cleanup(fail(MC_E_DEVICE, "pinned host allocation failed"));
     }
     h->host_last = h->host_rec + (size_t)NR * n_reps * (kRing + 1);
-    h->host_flag = (volatile uint32_t *)(h->host_last + (size_t)NR * n_reps);
-    *h->host_flag = 0;
     h->xcd_ok = device_deals_xcds(h, h->queues_dev);
     mc_status s;
     if ((s = plan_queues(h)) != MC_OK) return cleanup(s);

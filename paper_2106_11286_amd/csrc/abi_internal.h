@@ -96,7 +96,6 @@ struct mc_sim {
     double *host_rec = nullptr; // pinned, (kRing + 1) * n_reps * NR
     double *host_last = nullptr; // pinned, written by the device: records of the last
                                  // measured sweep of mc_sweep [n_reps][NR]
-    volatile uint32_t *host_flag = nullptr; // pinned: a team sweep's bounded wait gave up
     bool last_on_host = false;   // host_last holds the last measured sweep
     // team sweeps (kernels_team.hip): a workspace of the handle's own
     Tile default_tile{};         // the tile chosen by mc_init_lattice
@@ -110,7 +109,7 @@ struct mc_sim {
     mc::TeamWg *team_wgs = nullptr;
     uint64_t *team_words = nullptr;
     double *team_partials = nullptr;
-    uint32_t *team_state = nullptr; // epoch, abort, done[1 + n_reps]
+    uint32_t *team_state = nullptr; // epoch, redone, launch, done, ended[2 n_reps], left[n_reps]
     uint32_t team_grid = 0, team_lds = 0;
     int team_threads = 0;
     uint64_t t = 0;             // sweeps done

@@ -2,6 +2,7 @@
 // handles use them, how the planes are dealt to workgroups, and their launches.
 #include <algorithm>
 #include <cstdint>
+#include <cstdlib>
 #include <cstring>
 #include <vector>
 
@@ -15,12 +16,9 @@ namespace {
 constexpr uint32_t kTeamChunk = 64;
 // Sweeps per unmeasured launch (bounds one launch to some tens of ms).
 constexpr uint32_t kTeamLong = 4096;
-// Polls of a word before a workgroup gives up (about 0.5 us each).
-constexpr uint32_t kTeamSpins = 1u << 22;
-// Kernels that may hold the GPU beside one another (hardware queues of a
-// process); the workgroups of that many team launches fit the GPU together,
-// so each launch's workgroups all get to run whatever else is queued.
-constexpr uint32_t kTeamShare = 4;
+// Polls of a word before a workgroup gives up (about 0.5 us each, 30 ms in all;
+// mc_set_watchdog can lower it) and one workgroup does the launch's sweeps again.
+constexpr uint32_t kTeamSpins = 1u << 16;
 
 // A colour pass of its own launch takes about 4.4 us on a lattice this small
 // (sc 24^3 .. 64^3: 8.7 to 9.3 us per sweep, 14.5 to 15.4 measured).
@@ -95,6 +93,15 @@ TeamPlan plan_teams(const mc_sim *h, uint32_t q)
     return P;
 }
 
+// Kernels of this process that the GPU can run beside one another: HIP's
+// hardware queues, 4 unless the environment asks for more.
+uint32_t hardware_queues()
+{
+    const char *v = std::getenv("GPU_MAX_HW_QUEUES");
+    const long n = v ? std::strtol(v, nullptr, 10) : 0;
+    return (uint32_t)std::max(4l, std::min(n, 32l));
+}
+
 void team_bind(mc_sim *h, char *ws, bool owned)
 {
     h->team_ws = ws;
@@ -154,8 +161,11 @@ void team_init(mc_sim *h)
         if (n > 0) cus = std::min(cus, n);
     }
     const bool f64 = h->prec == MC_F64;
-    // the smallest share per workgroup whose launch fits the GPU kTeamShare
-    // times over
+    // the smallest share per workgroup whose launch fits the GPU `share` times
+    // over: team launches on as many streams then seldom wait for each other's
+    // workgroups to leave.  (Seldom, not never: other kernels and other
+    // processes take their part, too, which costs time, see kernels_team.hip.)
+    const uint32_t share = hardware_queues();
     TeamPlan P;
     bool found = false;
     for (uint32_t q = 64; q <= 8192 && !found; q += q / 8) {
@@ -169,11 +179,11 @@ void team_init(mc_sim *h)
             (void)hipGetLastError();
             return;
         }
-        found = P.wgs.size() * kTeamShare <= (size_t)cus * (size_t)std::max(0, per_cu);
+        found = P.wgs.size() * share <= (size_t)cus * (size_t)std::max(0, per_cu);
     }
     if (!found) return;
     uint64_t o = 0;
-    const uint64_t n_state = 2 + 1 + (uint64_t)h->n_reps;
+    const uint64_t n_state = 4 + 3 * (uint64_t)h->n_reps;
     h->team_off_wgs = (o = align_up(sizeof(uint32_t) * n_state, 256));
     h->team_off_words = (o = align_up(o + sizeof(TeamWg) * P.wgs.size(), 256));
     h->team_off_part = (o = align_up(o + sizeof(uint64_t) * P.words, 256));
@@ -236,9 +246,11 @@ mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, Team
     L.wgs = h->team_wgs;
     L.words = h->team_words;
     L.epoch = h->team_state;
-    L.abort = h->team_state + 1;
-    L.done = h->team_state + 2;
-    L.host_flag = const_cast<uint32_t *>(h->host_flag);
+    L.redone = h->team_state + 1;
+    L.launch = h->team_state + 2;
+    L.done = h->team_state + 3;
+    L.ended = h->team_state + 4;
+    L.left = L.ended + 2 * (size_t)h->n_reps;
     L.tctr_dev = h->tctr;
     L.partials = h->team_partials;
     L.records = h->records;
@@ -246,7 +258,7 @@ mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, Team
     L.seed_lo = (uint32_t)h->seed;
     L.seed_hi = (uint32_t)(h->seed >> 32);
     L.ring = kRing;
-    L.spin_limit = kTeamSpins;
+    L.spin_limit = std::min(kTeamSpins, h->spin_limit);
     for (uint32_t done = 0; done < n;) {
         const uint32_t k = std::min(measure ? kTeamChunk : kTeamLong, n - done);
         L.n_sweeps = k;
@@ -261,3 +273,29 @@ mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, Team
 }
 
 } // namespace mcabi
+
+extern "C" mc_status mc_get_team(mc_sim *h, int32_t replica, int32_t *workgroups, int32_t *planes,
+                                 int32_t *last_planes, uint64_t *redone)
+{
+    if (!alive(h)) return fail(MC_E_STATE, "invalid or destroyed handle");
+    if (replica < 0 || replica >= h->n_reps)
+        return fail(MC_E_ARG, "replica %d out of range [0, %d)", replica, h->n_reps);
+    int32_t n = 0, first = 0, last = 0;
+    if (h->team_on)
+        for (const TeamWg &w : h->team_table)
+            if (w.rep == (uint32_t)replica) {
+                if (n++ == 0) first = w.nz;
+                last = w.nz;
+            }
+    if (workgroups) *workgroups = n;
+    if (planes) *planes = first;
+    if (last_planes) *last_planes = last;
+    if (!redone) return MC_OK;
+    *redone = 0;
+    if (!h->team_on) return MC_OK;
+    uint32_t v = 0;
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    HIP_TRY(hipMemcpy(&v, h->team_state + 1, sizeof v, hipMemcpyDeviceToHost));
+    *redone = v;
+    return MC_OK;
+}

@@ -119,10 +119,12 @@ struct TeamLaunch {
     const RepDev *reps_dev;
     const TeamWg *wgs;
     uint64_t *words;
-    uint32_t *done;          // [1 + n_reps] finished workgroups (zero between launches)
+    uint32_t *done;          // workgroups through with the launch (zero between launches)
+    uint32_t *ended;         // [n_reps][2] how each team's launch ends (even, odd launches)
+    uint32_t *launch;        // launches so far
+    uint32_t *left;          // [n_reps] workgroups that left for a redo (zero between launches)
+    uint32_t *redone;        // teams' launches done again by one workgroup so far
     uint32_t *epoch;         // tags used so far
-    uint32_t *abort;         // epoch + 1 of a launch whose wait gave up
-    uint32_t *host_flag;     // host-visible: a wait gave up
     uint32_t *tctr_dev;      // sweep counter (advanced by the launch)
     double *partials;        // [n_sweeps][grid][NQ] (measured launches)
     double *records;         // ring [ring][n_reps][NR]

@@ -110,6 +110,9 @@ _SIGNATURES = {
     "mc_num_colours": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32)]),
     "mc_series_stats": (ctypes.c_int, [ctypes.POINTER(Obs), ctypes.c_uint64, ctypes.c_uint64,
                                        ctypes.c_double, ctypes.POINTER(Stats)]),
+    "mc_get_team": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32),
+                                   ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32),
+                                   ctypes.POINTER(ctypes.c_uint64)]),
     "mc_set_watchdog": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_uint32]),
     "mc_set_persistent_mode": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int]),
     "mc_block_workspace": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_uint32,
@@ -400,6 +403,16 @@ class Simulation:
     def synchronize_checked(self):
         """``mc_synchronize``: wait and report deferred errors."""
         _check("mc_synchronize", LIB.mc_synchronize(self.handle))
+
+    def team(self, r: int = 0) -> dict:
+        """``mc_get_team``: workgroups of replica r's team (0: its sweeps do not
+        run by teams), planes of the first and the last of them, and the
+        handle's teams' launches done again after a wait gave up."""
+        v, n = [ctypes.c_int32() for _ in range(3)], ctypes.c_uint64()
+        _check("mc_get_team", LIB.mc_get_team(self.handle, int(r), *[ctypes.byref(x) for x in v],
+                                              ctypes.byref(n)))
+        return {"workgroups": v[0].value, "planes": v[1].value, "last_planes": v[2].value,
+                "redone": n.value}
 
     def set_watchdog(self, spins: int):
         _check("mc_set_watchdog", LIB.mc_set_watchdog(self.handle, int(spins)))
