@@ -190,8 +190,9 @@ mc_status mc_sweep(mc_sim *h, uint32_t n_sweeps, uint32_t flags);
 
 /* mc_sweep with HIP events recorded on the handle's stream around every
  * colour-pass launch; synchronises and returns the mean duration of one pass
- * launch (with the fused sweep kernel 9: of its one launch per sweep) and the
- * total time of the call (milliseconds).  For measuring the kernels in place;
+ * launch (with the fused sweep kernel 9: of its one launch per sweep; where
+ * whole sweeps are one launch, kernel 3 and teams: the time per colour of a
+ * sweep) and the total time of the call (milliseconds).  For measuring the kernels in place;
  * results are identical to mc_sweep. */
 mc_status mc_sweep_timed(mc_sim *h, uint32_t n_sweeps, uint32_t flags, double *pass_ms_avg,
                          double *total_ms);
@@ -299,8 +300,8 @@ mc_status mc_set_sweep(mc_sim *h, uint64_t t);
  *    other lattices of up to 400,000 box sites in all, a team of workgroups
  *    per replica runs the sweeps instead where that is faster: each holds a
  *    share of the planes in LDS and exchanges its boundary planes with its
- *    neighbours after every colour; choosing a tile ends it (the chain is the
- *    same).  Single passes (mc_debug_pass, mc_measure_state) keep using the
+ *    neighbours after every colour; choosing another tile ends it and
+ *    choosing the default one brings it back (the chain is the same).  Single passes (mc_debug_pass, mc_measure_state) keep using the
  *    previous pass kernel.  A replica too large gives MC_E_UNSUPPORTED;
  *  kernel 4 (sc only, every row of an even number of packed columns; the
  *    default when every row also has at least 96 packed columns and four

@@ -1223,7 +1223,7 @@ mc_status mc_sweep_timed(mc_sim *h, uint32_t n_sweeps, uint32_t flags, double *p
     if (n_sweeps == 0) return fail(MC_E_ARG, "n_sweeps must be >= 1");
     if (h->t + n_sweeps > 0xFFFFFFFFull) return fail(MC_E_STATE, "sweep counter would exceed 2^32-1");
     const bool measure = flags & MC_MEASURE;
-    if (h->tile.kernel == KERNEL_LDS) {
+    if (h->team_on || h->tile.kernel == KERNEL_LDS) {
         // whole sweeps in one launch: the pass time reported is the average
         // share of a colour pass
         hipEvent_t e0, e1;
@@ -1622,7 +1622,7 @@ mc_status mc_set_tile(mc_sim *h, int32_t kernel, int32_t tx, int32_t ty, int32_t
         h->team_on = false;
         h->tile = Tile{KERNEL_LDS, tx, 1, 1};
         h->tuned_persistent = false; // a tile set by hand runs per pass under MC_TUNED_LAUNCH
-        return MC_OK;
+        return team_resume(h);
     }
     Tile t{kernel, tx, ty, zc};
     uint64_t max_bytes = 0;
@@ -1724,7 +1724,8 @@ mc_status mc_set_tile(mc_sim *h, int32_t kernel, int32_t tx, int32_t ty, int32_t
     HIP_TRY(hipMemcpyAsync(h->work_dev, h->work.data(), sizeof(WorkItem) * h->work.size(),
                            hipMemcpyHostToDevice, h->stream));
     if ((st = plan_queues(h)) != MC_OK) return st;
-    return upload_reps(h);
+    if ((st = upload_reps(h)) != MC_OK) return st;
+    return team_resume(h);
 }
 
 mc_status mc_get_tile(const mc_sim *h, int32_t *kernel, int32_t *tx, int32_t *ty, int32_t *zc,

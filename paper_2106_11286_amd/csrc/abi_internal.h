@@ -53,6 +53,10 @@ uint64_t align_up(uint64_t v, uint64_t a);
 int row_len(const mc_replica_desc &d);
 int pow2_at_least(int v);
 uint64_t xy_tiles(const mc_replica_desc &d, const Tile &t);
+inline bool same_tile(const Tile &a, const Tile &b)
+{
+    return a.kernel == b.kernel && a.tx == b.tx && a.ty == b.ty && a.zc == b.zc;
+}
 bool persistent_supported(const Tile &t);
 void set_temperature(RepDev &R, double T);
 
@@ -141,6 +145,8 @@ void team_release(mc_sim *h);
 // workspace it moves to device memory of the library's; the teams stay off if
 // there is none.
 hipError_t team_activate(mc_sim *h);
+// After a tile change: the teams run again if the tile is the handle's default.
+mc_status team_resume(mc_sim *h);
 // Offset of a workspace of `need` bytes at the end of the scratch, clear of a
 // layout of `used` bytes, or kTeamNoRoom.
 constexpr uint64_t kTeamNoRoom = ~0ull;

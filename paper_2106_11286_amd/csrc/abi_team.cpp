@@ -232,6 +232,14 @@ hipError_t team_activate(mc_sim *h)
                           hipMemcpyHostToDevice, h->stream);
 }
 
+mc_status team_resume(mc_sim *h)
+{
+    if (!h->team_ws || !same_tile(h->tile, h->default_tile)) return MC_OK;
+    HIP_TRY(team_activate(h));
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    return MC_OK;
+}
+
 void team_release(mc_sim *h)
 {
     if (h->team_ws && h->team_owned) (void)hipFree(h->team_ws);

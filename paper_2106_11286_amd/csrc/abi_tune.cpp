@@ -103,20 +103,13 @@ std::vector<Tile> tile_candidates(const mc_sim *h, uint32_t flags)
     return out;
 }
 
-// Choose a tile; the teams run whenever the choice is the handle's default.
+// Choose a tile, its sweeps by teams (the handle's default only) or not.
 mc_status choose_tile(mc_sim *h, const Tile &t, bool teams)
 {
     const Tile d = t.kernel == TEAM_CANDIDATE ? h->default_tile : t;
     const mc_status st = mc_set_tile(h, d.kernel, d.tx, d.ty, d.zc);
-    if (st != MC_OK || !teams || !h->team_ws) return st;
-    HIP_TRY(team_activate(h));
-    HIP_TRY(hipStreamSynchronize(h->stream));
-    return MC_OK;
-}
-
-bool same_tile(const Tile &a, const Tile &b)
-{
-    return a.kernel == b.kernel && a.tx == b.tx && a.ty == b.ty && a.zc == b.zc;
+    if (!teams) h->team_on = false;
+    return st;
 }
 
 std::string tune_key(const mc_sim *h, uint32_t flags)
