@@ -373,7 +373,7 @@ mc_status mc_get_tile(const mc_sim *h, int32_t *kernel, int32_t *tx, int32_t *ty
  * fastest (the fused sweep kernel 9 is a candidate once every replica has a
  * second buffer set).  The trial sweeps are ordinary sweeps of the chain: they advance
  * the state and the sweep counter (results stay bitwise independent of the
- * shape).  cache_path (may be NULL) names a text file of earlier choices
+ * shape); those of the team sweeps (see kernel 3) are taken back.  cache_path (may be NULL) names a text file of earlier choices
  * keyed by device (mc_tune_device_key of the handle's device), lattices,
  * precision and flags; a matching entry skips the trials, a new choice is
  * appended.  The chosen shape is returned through the out pointers (each may

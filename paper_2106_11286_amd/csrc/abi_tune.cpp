@@ -12,13 +12,11 @@
 
 using namespace mcabi;
 
-namespace {
+namespace mcabi {
 
 // Candidate shapes for the autotuner: each kernel family with a few tile
 // widths, rows per thread and plane chunks aimed at 2k .. 24k workgroups.
-constexpr int32_t TEAM_CANDIDATE = -1; // the default tile, swept by teams
-
-std::vector<Tile> tile_candidates(const mc_sim *h, uint32_t flags)
+std::vector<Tile> tile_candidates(const mc_sim *h)
 {
     int W = 1, Ly = 1;
     for (const auto &d : h->desc) {
@@ -95,20 +93,81 @@ std::vector<Tile> tile_candidates(const mc_sim *h, uint32_t flags)
             out.push_back(t);
         }
     }
-    // small lattices swept by teams: that default stands in for the narrowest
-    // workgroup (the LDS kernel's smallest, else the narrowest tile), so the
-    // chain advances by as many trial sweeps with and without it
-    if (h->team_ws && !(flags & MC_PERSISTENT) && !out.empty())
-        (lds_fits(h) ? out.front() : out.back()) = Tile{TEAM_CANDIDATE, 0, 0, 0};
     return out;
 }
+
+} // namespace mcabi
+
+namespace {
 
 // Choose a tile, its sweeps by teams (the handle's default only) or not.
 mc_status choose_tile(mc_sim *h, const Tile &t, bool teams)
 {
-    const Tile d = t.kernel == TEAM_CANDIDATE ? h->default_tile : t;
-    const mc_status st = mc_set_tile(h, d.kernel, d.tx, d.ty, d.zc);
+    const mc_status st = mc_set_tile(h, t.kernel, t.tx, t.ty, t.zc);
     if (!teams) h->team_on = false;
+    return st;
+}
+
+// Time `sweeps` sweeps in the launch mode of `flags`, after one for warmth.
+mc_status time_sweeps(mc_sim *h, uint32_t sweeps, uint32_t flags, hipEvent_t e0, hipEvent_t e1,
+                      float *ms)
+{
+    mc_status st = mc_sweep(h, 1, flags);
+    if (st == MC_OK) st = mc_synchronize(h);
+    if (st != MC_OK) return st;
+    (void)hipEventRecord(e0, h->stream);
+    st = mc_sweep(h, sweeps, flags);
+    (void)hipEventRecord(e1, h->stream);
+    if (st == MC_OK) st = mc_synchronize(h);
+    if (st == MC_OK) (void)hipEventElapsedTime(ms, e0, e1);
+    return st;
+}
+
+// The teams' time, without a step of the chain: the trial sweeps of the other
+// candidates are the same with and without teams, and so is the state after
+// them.  *ms stays as it is where the teams cannot run or there is no memory for
+// a copy of the spins.
+mc_status time_teams(mc_sim *h, uint32_t sweeps, uint32_t flags, hipEvent_t e0, hipEvent_t e1,
+                     float *ms)
+{
+    if (choose_tile(h, h->default_tile, true) != MC_OK || !h->team_on) return MC_OK;
+    mc_status st = MC_OK;
+    const size_t esz = h->prec == MC_F64 ? sizeof(double) : sizeof(float);
+    uint64_t bytes = 0;
+    for (const RepDev &R : h->reps) bytes += 3 * esz * R.n_box;
+    char *copy = nullptr;
+    if (hipMalloc((void **)&copy, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return MC_OK;
+    }
+    auto move = [&](bool save) {
+        char *c = copy;
+        hipError_t e = hipSuccess;
+        for (const RepDev &R : h->reps)
+            for (void *plane : {R.sx, R.sy, R.sz}) {
+                if (e == hipSuccess)
+                    e = hipMemcpyAsync(save ? (void *)c : plane, save ? plane : (void *)c,
+                                       esz * R.n_box, hipMemcpyDeviceToDevice, h->stream);
+                c += esz * R.n_box;
+            }
+        return e == hipSuccess ? hipStreamSynchronize(h->stream) : e;
+    };
+    const uint64_t t = h->t, n_measured = h->n_measured;
+    const int64_t last_slot = h->last_slot;
+    const bool last_on_host = h->last_on_host;
+    hipError_t e = move(true);
+    if (e == hipSuccess) {
+        st = time_sweeps(h, sweeps, flags, e0, e1, ms);
+        e = move(false);
+        const mc_status back = mc_set_sweep(h, t);
+        if (st == MC_OK) st = back;
+        h->n_measured = n_measured;
+        h->last_slot = last_slot;
+        h->last_on_host = last_on_host;
+    }
+    (void)hipFree(copy);
+    if (st == MC_OK && e != hipSuccess)
+        st = fail(MC_E_DEVICE, "autotuner: %s", hipGetErrorString(e));
     return st;
 }
 
@@ -177,8 +236,9 @@ mc_status mc_autotune(mc_sim *h, uint32_t trial_sweeps, uint32_t flags, const ch
     const bool tune_launch = (flags & MC_TUNED_LAUNCH) != 0;
     if (trial_sweeps < 1) return fail(MC_E_ARG, "trial_sweeps must be >= 1");
     const std::string key = tune_key(h, flags);
-    Tile best = h->tile;
-    bool best_pers = false;
+    const Tile before = h->tile;
+    Tile best = before;
+    bool best_pers = false, best_team = false;
     bool found = false;
     if (cache_path) {
         std::ifstream in(cache_path);
@@ -188,75 +248,65 @@ mc_status mc_autotune(mc_sim *h, uint32_t trial_sweeps, uint32_t flags, const ch
             std::string k;
             Tile t;
             double ms;
-            int pers = 0;
+            int pers = 0, team = 0;
             if (ls >> k >> t.kernel >> t.tx >> t.ty >> t.zc >> ms && k == key) {
+                // entries without the last fields: per pass, not by teams
                 if (!(ls >> pers)) pers = 0;
+                if (!(ls >> team)) team = 0;
                 best = t;
                 best_pers = tune_launch && pers == 1;
+                best_team = team == 1 && same_tile(t, h->default_tile);
                 found = true;
             }
         }
     }
     if (found) {
-        const bool teams = same_tile(best, h->default_tile) && !(flags & MC_PERSISTENT);
-        if (choose_tile(h, best, teams) != MC_OK) found = false; // stale entry: tune again
+        if (choose_tile(h, best, best_team) != MC_OK) found = false; // stale entry: tune again
     }
     if (!found) {
         hipEvent_t e0, e1;
         HIP_TRY(hipEventCreate(&e0));
         HIP_TRY(hipEventCreate(&e1));
-        double best_ms = 1e300;
-        for (const Tile &t : tile_candidates(h, flags)) {
-            const bool team = t.kernel == TEAM_CANDIDATE;
-            const Tile &run = team ? h->default_tile : t;
-            if ((flags & MC_PERSISTENT) && !persistent_supported(run)) continue;
-            if (choose_tile(h, t, team) != MC_OK) continue; // e.g. too big
+        float best_ms = 1e30f;
+        mc_status st = MC_OK;
+        best = before;
+        best_pers = best_team = false;
+        if (h->team_ws && !(flags & MC_PERSISTENT)) {
+            st = time_teams(h, trial_sweeps, flags & ~MC_TUNED_LAUNCH, e0, e1, &best_ms);
+            best_team = best_ms < 1e30f;
+            if (best_team) best = h->default_tile;
+        }
+        for (const Tile &t : tile_candidates(h)) {
+            if (st != MC_OK) break;
+            if ((flags & MC_PERSISTENT) && !persistent_supported(t)) continue;
+            if (choose_tile(h, t, false) != MC_OK) continue; // e.g. too big
             // launch modes to time: as asked, or (MC_TUNED_LAUNCH) both
-            for (int mode = 0; mode < 2; ++mode) {
+            for (int mode = 0; mode < 2 && st == MC_OK; ++mode) {
                 uint32_t f = flags & ~MC_TUNED_LAUNCH;
                 if (mode == 1) {
-                    if (!tune_launch || !persistent_supported(run) || run.kernel == KERNEL_LDS)
-                        break;
+                    if (!tune_launch || !persistent_supported(t) || t.kernel == KERNEL_LDS) break;
                     f |= MC_PERSISTENT;
                 }
-                mc_status st = mc_sweep(h, 1, f);
-                if (st == MC_OK) st = mc_synchronize(h);
-                if (st != MC_OK) {
-                    (void)hipEventDestroy(e0);
-                    (void)hipEventDestroy(e1);
-                    return st;
-                }
-                (void)hipEventRecord(e0, h->stream);
-                st = mc_sweep(h, trial_sweeps, f);
-                (void)hipEventRecord(e1, h->stream);
-                if (st == MC_OK) st = mc_synchronize(h);
-                if (st != MC_OK) {
-                    (void)hipEventDestroy(e0);
-                    (void)hipEventDestroy(e1);
-                    return st;
-                }
                 float ms = 0.f;
-                (void)hipEventElapsedTime(&ms, e0, e1);
-                if (ms < best_ms) {
+                st = time_sweeps(h, trial_sweeps, f, e0, e1, &ms);
+                if (st == MC_OK && ms < best_ms) {
                     best_ms = ms;
                     best = t;
                     best_pers = mode == 1;
+                    best_team = false;
                 }
             }
         }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
-        const mc_status st = choose_tile(h, best, best.kernel == TEAM_CANDIDATE);
+        if (st == MC_OK) st = choose_tile(h, best, best_team);
         if (st != MC_OK) return st;
-        best = h->tile;
         if (cache_path) {
             std::ofstream out(cache_path, std::ios::app);
-            if (out) {
+            if (out)
                 out << key << " " << best.kernel << " " << best.tx << " " << best.ty << " "
-                    << best.zc << " " << best_ms / trial_sweeps;
-                if (tune_launch) out << " " << (best_pers ? 1 : 0);
-                out << "\n";
-            }
+                    << best.zc << " " << (double)best_ms / trial_sweeps << " " << (best_pers ? 1 : 0)
+                    << " " << (best_team ? 1 : 0) << "\n";
         }
     }
     if (tune_launch) h->tuned_persistent = best_pers;
