@@ -272,7 +272,8 @@ mc_status mc_debug_pass(mc_sim *h, int32_t colour, void *const *dh, void *const 
 /* Copy a replica's spins between the library layout and natural order
  * (canonical index s, see above) on the device.  to_natural != 0: packed ->
  * natural; 0: natural -> packed.  nx, ny, nz are device arrays of
- * mc_required_sites elements of the precision's type. */
+ * mc_required_sites elements of the precision's type.  Synchronises and, with
+ * the copy done, reports a deferred error of a persistent launch. */
 mc_status mc_layout_copy(mc_sim *h, int32_t replica, int32_t to_natural, void *nx, void *ny,
                          void *nz);
 
@@ -472,7 +473,8 @@ mc_status mc_exchange_state(mc_sim *h, int32_t *replica_at_slot, double *T_slot,
  * attempts (occupied chosen sites), accepted moves and conflicts (attempts
  * with an attempted nearest neighbour in the same step, counted with
  * MC_BLOCK_CONFLICTS only); MC_BLOCK_RESET zeroes them first.
- * mc_block_counts synchronises, returns the three counts and zeroes them. */
+ * mc_block_counts synchronises, returns the three counts, zeroes them and
+ * reports a deferred error of a persistent launch. */
 #define MC_BLOCK_CONFLICTS 4u
 #define MC_BLOCK_RESET 8u
 mc_status mc_block_workspace(const mc_sim *h, uint32_t n, uint64_t *bytes);

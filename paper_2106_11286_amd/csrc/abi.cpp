@@ -1553,7 +1553,7 @@ mc_status mc_layout_copy(mc_sim *h, int32_t replica, int32_t to_natural, void *n
     HIP_TRY(launch_layout(h->prec == MC_F64, h->kind, &h->reps[replica], to_natural != 0, nx, ny,
                           nz, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
-    return MC_OK;
+    return check_persistent(h);
 }
 
 mc_status mc_set_second_buffers(mc_sim *h, const mc_spin_buffers *bufs)

@@ -227,7 +227,7 @@ mc_status mc_block_counts(mc_sim *h, void *work, uint64_t counts[3])
     HIP_TRY(hipMemcpy(counts, work, 3 * sizeof(uint64_t), hipMemcpyDeviceToHost));
     HIP_TRY(launch_zero_u32((uint32_t *)work, 6, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
-    return MC_OK;
+    return check_persistent(h);
 }
 
 } // extern "C"
