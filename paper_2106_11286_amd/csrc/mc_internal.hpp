@@ -106,6 +106,19 @@ constexpr int lband_slots_needed(int rows, int lxh, int esz, int n_waves)
     return (int)((3u * lband_comp_chunks(rows, lxh, esz) / 64u + (uint32_t)n_waves - 1) / (uint32_t)n_waves);
 }
 
+// Row of a lattice of Ly rows that a tile of the LDS-staged band kernel stages in
+// the place of row y (y >= -1): y itself, the row across a periodic face for the
+// rows next to the lattice, none (-1) for rows beyond an open face and for those
+// further out, which no site of the tile has for a neighbour.  (A tile may hold
+// many more rows than the lattice.)
+constexpr int lband_row(int y, int Ly, bool periodic)
+{
+    return y >= 0 && y < Ly           ? y
+           : periodic && y == -1      ? Ly - 1
+           : periodic && y == Ly      ? 0
+                                      : -1;
+}
+
 // Tile of one workgroup: tx row columns x ty rows x zc planes, and the kernel
 // that maps it onto threads.
 struct Tile {

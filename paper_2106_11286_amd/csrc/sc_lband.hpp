@@ -72,8 +72,7 @@ __device__ __forceinline__ void sc_lband_body(const PassLaunch &P, int colour, u
         uint32_t off[LBAND_SLOTS]; // element offset within a plane; ~0u: nothing to copy
         int n;                     // slots of this wave
     };
-    // rows ybase .. ybase+n_rows-1 (wrapped on a periodic y axis, skipped
-    // beyond an open face)
+    // rows ybase .. ybase+n_rows-1 where they exist (lband_row)
     auto make_slots = [&](int ybase, int n_rows, uint32_t cs) __attribute__((always_inline)) {
         Slots sl;
         const int gpc = (int)(cs / 64u); // chunk groups per component
@@ -88,11 +87,8 @@ __device__ __forceinline__ void sc_lband_body(const PassLaunch &P, int colour, u
             const int cc = (g % gpc) * 64 + lane;
             if (cc >= n_rows * row_chunks) continue;
             const int k = cc / row_chunks, col = (cc - k * row_chunks) * CH;
-            int y = ybase + k;
-            if (y < 0 || y >= Ly) {
-                if (!py) continue;
-                y = y < 0 ? y + Ly : y - Ly;
-            }
+            const int y = lband_row(ybase + k, Ly, py);
+            if (y < 0) continue;
             sl.off[j] = (uint32_t)y * (uint32_t)Lxh + (uint32_t)col;
         }
         return sl;
@@ -128,7 +124,7 @@ __device__ __forceinline__ void sc_lband_body(const PassLaunch &P, int colour, u
         stage(dst, sl_o, cs_o, oth, n);
     };
     auto stage_own = [&](int n) __attribute__((always_inline)) {
-        // rows past Ly (a ragged last tile) hold no site; they wrap or are skipped
+        // rows past Ly (a ragged last tile) hold no site
         stage(own_buf((unsigned)n & 1u), sl_w, cs_w, own, n);
     };
 
