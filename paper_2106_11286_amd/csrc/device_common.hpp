@@ -186,10 +186,10 @@ __device__ __forceinline__ bool logical_item(const PassLaunch &P, uint32_t &item
 }
 
 // Sweep counter of a colour pass, and what its launch leaves for the next one.
-// Each colour has a counter of its own: a pass reads its colour's and, when its
-// sites are done, writes the next colour's (after the last colour t + 1 into
-// the first's), so no launch writes what it reads and none is spent on
-// advancing a counter.
+// In the last of the sweeps that are enqueued together each colour has a counter
+// of its own: a pass reads its colour's and, when its sites are done, writes the
+// next colour's (after the last colour t + 1 into the first's), so no launch
+// writes what it reads and none is spent on advancing a counter.
 __device__ __forceinline__ uint32_t pass_sweep(const PassLaunch &P) { return *P.tctr_dev + P.t_off; }
 __device__ __forceinline__ void pass_done(const PassLaunch &P, uint32_t t)
 {

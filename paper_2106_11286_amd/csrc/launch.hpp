@@ -8,7 +8,10 @@
 
 namespace mc {
 
-// Everything a pass launch needs; device pointers point into the scratch.
+// Everything a pass launch needs; device pointers point into the scratch.  What
+// every workgroup reads at its start comes first, what one reads at its end last
+// (with the next counter in front of the seeds an unmeasured sweep of fcc 64^3
+// took 21.7 us, so 20.9; sc 96^3 14.7, 14.2).
 struct PassLaunch {
     const RepDev *reps_dev;   // [n_reps]
     const WorkItem *work_dev; // [n_items]
@@ -17,8 +20,6 @@ struct PassLaunch {
     uint32_t n_items;         // items in the whole work list (partials stride)
     const uint32_t *tctr_dev; // sweep counter t (device)
     uint32_t t_off;           // added to t
-    uint32_t *tctr_next;      // the next pass's counter, written t + t_inc (or null)
-    uint32_t t_inc;
     uint32_t seed_lo, seed_hi;
     Tile tile;
     double *partials_dev;     // [n_colours][n_items][NQ]
@@ -26,6 +27,8 @@ struct PassLaunch {
     uint8_t *dbg_acc;         // debug: per-site decision (or null)
     uint32_t lds_bytes;       // dynamic LDS of the LDS-staged pass kernel
     int32_t lds_positions;    // its (row, pair) positions per lane (1 or 2)
+    uint32_t t_inc;           // the next pass's counter is left at t + t_inc
+    uint32_t *tctr_next;      // (null: none)
 };
 
 // mode: 0 = Metropolis update, 1 = observables of the current state only,
