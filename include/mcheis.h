@@ -299,11 +299,12 @@ mc_status mc_set_sweep(mc_sim *h, uint64_t t);
  *    (64 .. 1024, multiple of 64) per replica, colour passes separated by
  *    workgroup barriers; ty and zc are ignored.  On the default tile, also of
  *    other lattices of up to 400,000 box sites in all, a team of workgroups
- *    per replica runs the sweeps instead where that is faster: each holds a
+ *    per replica runs the sweeps instead where that is faster, which depends on
+ *    the lattices and on the sweeps of the call (mc_get_team): each holds a
  *    share of the planes in LDS and exchanges its boundary planes with its
- *    neighbours after every colour; choosing another tile ends it and
- *    choosing the default one brings it back (the chain is the same).  Single passes (mc_debug_pass, mc_measure_state) keep using the
- *    previous pass kernel.  A replica too large gives MC_E_UNSUPPORTED;
+ *    neighbours after every colour; choosing another tile ends it and choosing
+ *    the default one brings it back (the chain is the same).  Single passes
+ *    (mc_debug_pass, mc_measure_state) keep using the previous pass kernel.  A replica too large gives MC_E_UNSUPPORTED;
  *  kernel 4 (sc only, every row of an even number of packed columns; the
  *    default when every row also has at least 96 packed columns and four
  *    fifths of the lanes hold a pair): as kernel 1 with two adjacent columns
@@ -412,11 +413,13 @@ mc_status mc_series_stats(const mc_obs *series, uint64_t n, uint64_t stride, dou
 
 /* Team sweeps (see kernel 3 of mc_set_tile) of one replica: workgroups of its
  * team (0 where the sweeps of the tile in force do not run by teams), planes of
- * the team's first and of its last workgroup, and how many teams' launches of
+ * the team's first and of its last workgroup, how many sweeps a call (or a
+ * schedule's chunk of up to 64) has to ask for to be run by the teams,
+ * unmeasured and measured (UINT32_MAX: none is), and how many teams' launches of
  * the handle were done again by one workgroup so far because a wait gave up.
  * The out pointers may be NULL; with `redone` the call synchronises. */
 mc_status mc_get_team(mc_sim *h, int32_t replica, int32_t *workgroups, int32_t *planes,
-                      int32_t *last_planes, uint64_t *redone);
+                      int32_t *last_planes, uint32_t from_sweeps[2], uint64_t *redone);
 
 /* Bounded wait of persistent launches: a work unit waiting for its replica's
  * previous pass gives up after `spins` polls (about 0.1 us each; default

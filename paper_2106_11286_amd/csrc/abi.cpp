@@ -625,7 +625,7 @@ hipError_t finalize_sweep(mc_sim *h, uint32_t slot, uint32_t t_add, bool to_host
 // capture.
 mc_status enqueue_sweeps(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool to_host = false)
 {
-    if (h->team_on)
+    if (team_takes(h, n, measure))
         return enqueue_team(h, n, measure, slot0, to_host ? TeamHost::last : TeamHost::none);
     if (h->tile.kernel == KERNEL_LDS) return enqueue_lds(h, n, measure, slot0);
     const bool f64 = h->prec == MC_F64;
@@ -771,8 +771,8 @@ bool persistent_supported(const Tile &t)
 mc_status enqueue_persistent(mc_sim *h, uint32_t n, bool measure, uint32_t slot0)
 {
     if (h->tile.kernel == KERNEL_LDS)
-        return h->team_on ? enqueue_team(h, n, measure, slot0, TeamHost::none)
-                          : enqueue_lds(h, n, measure, slot0);
+        return team_takes(h, n, measure) ? enqueue_team(h, n, measure, slot0, TeamHost::none)
+                                         : enqueue_lds(h, n, measure, slot0);
     if (!persistent_supported(h->tile))
         return fail(MC_E_UNSUPPORTED, "persistent sweeps: no kernel for this tile (%d rows "
                                       "per thread); use strips of 2 or 4 rows, pairs of 1 or "
@@ -928,12 +928,18 @@ void note_sweeps(mc_sim *h, uint64_t n)
     }
 }
 
+// Whether a chunk of a schedule runs by teams.
+bool team_chunk(const mc_sim *h, uint32_t n, bool measure, bool persistent)
+{
+    return team_takes(h, n, measure) && (!persistent || h->tile.kernel == KERNEL_LDS);
+}
+
 mc_status run_chunk(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, bool persistent)
 {
     if (n == 0) return MC_OK;
     // a chunk of team sweeps is one launch, which leaves its records in pinned
     // memory: nothing to replay or to copy
-    if (h->team_on && (!persistent || h->tile.kernel == KERNEL_LDS))
+    if (team_chunk(h, n, measure, persistent))
         return enqueue_team(h, n, measure, slot0, TeamHost::all);
     if (!h->stream) {
         const mc_status s = persistent ? enqueue_persistent(h, n, measure, slot0)
@@ -1206,7 +1212,8 @@ mc_status mc_sweep(mc_sim *h, uint32_t n_sweeps, uint32_t flags)
     if (h->t + n_sweeps > 0xFFFFFFFFull) return fail(MC_E_STATE, "sweep counter would exceed 2^32-1");
     const bool measure = flags & MC_MEASURE;
     const uint32_t slot0 = (uint32_t)(h->n_measured % kRing);
-    const bool to_host = !(flags & MC_PERSISTENT) && (h->team_on || h->tile.kernel != KERNEL_LDS);
+    const bool to_host = !(flags & MC_PERSISTENT) &&
+                         (h->tile.kernel != KERNEL_LDS || team_takes(h, n_sweeps, measure));
     mc_status s = (flags & MC_PERSISTENT)
                       ? enqueue_persistent(h, n_sweeps, measure, slot0)
                       : enqueue_sweeps(h, n_sweeps, measure, slot0, to_host);
@@ -1230,7 +1237,8 @@ mc_status mc_sweep_timed(mc_sim *h, uint32_t n_sweeps, uint32_t flags, double *p
     if (n_sweeps == 0) return fail(MC_E_ARG, "n_sweeps must be >= 1");
     if (h->t + n_sweeps > 0xFFFFFFFFull) return fail(MC_E_STATE, "sweep counter would exceed 2^32-1");
     const bool measure = flags & MC_MEASURE;
-    if (h->team_on || h->tile.kernel == KERNEL_LDS) {
+    const bool team = team_takes(h, n_sweeps, measure);
+    if (team || h->tile.kernel == KERNEL_LDS) {
         // whole sweeps in one launch: the pass time reported is the average
         // share of a colour pass
         hipEvent_t e0, e1;
@@ -1239,7 +1247,7 @@ mc_status mc_sweep_timed(mc_sim *h, uint32_t n_sweeps, uint32_t flags, double *p
         const uint32_t slot0 = (uint32_t)(h->n_measured % kRing);
         hipError_t err = hipEventRecord(e0, h->stream);
         mc_status st = err != hipSuccess ? MC_OK
-                       : h->team_on      ? enqueue_team(h, n_sweeps, measure, slot0, TeamHost::none)
+                       : team            ? enqueue_team(h, n_sweeps, measure, slot0, TeamHost::none)
                                          : enqueue_lds(h, n_sweeps, measure, slot0);
         if (err == hipSuccess && st == MC_OK) err = hipEventRecord(e1, h->stream);
         if (err == hipSuccess && st == MC_OK) err = hipEventSynchronize(e1);
@@ -1455,7 +1463,7 @@ mc_status mc_run_schedule(mc_sim *h, const mc_schedule *s, mc_obs *series, uint6
             h->last_on_host = false;
             h->last_slot = k - 1;
             const size_t sz = sizeof(double) * NR * h->n_reps * k;
-            if (!h->team_on || (persistent && h->tile.kernel != KERNEL_LDS))
+            if (!team_chunk(h, k, true, persistent))
                 HIP_TRY(hipMemcpyAsync(h->host_rec, h->records, sz, hipMemcpyDeviceToHost,
                                        h->stream));
             HIP_TRY(hipStreamSynchronize(h->stream));

@@ -114,6 +114,8 @@ struct mc_sim {
     uint64_t *team_words = nullptr;
     double *team_partials = nullptr;
     uint32_t *team_state = nullptr; // epoch, redone, launch, done, ended[2 n_reps], left[n_reps]
+    uint32_t team_from[2] = {~0u, ~0u}; // sweeps of a call, unmeasured and measured, from
+                                        // which the teams are the faster way
     uint32_t team_grid = 0, team_lds = 0;
     int team_threads = 0;
     uint64_t t = 0;             // sweeps done
@@ -156,6 +158,9 @@ bool team_disjoint(const mc_sim *h);
 // Records of a measured team launch in pinned memory besides the device ring:
 // none, the last sweep's (host_last), or all at their ring slots (host_rec).
 enum class TeamHost { none, last, all };
+// Whether n sweeps enqueued together run by the handle's teams.
+constexpr uint32_t kTeamNever = ~0u;
+bool team_takes(const mc_sim *h, uint32_t n, bool measure);
 mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, TeamHost host);
 // A simple-cubic handle with a replica cut to a sphere (tile and LDS kernels only).
 bool sc_sphere(const mc_sim *h);

@@ -20,8 +20,7 @@ constexpr uint32_t kTeamLong = 4096;
 // mc_set_watchdog can lower it) and one workgroup does the launch's sweeps again.
 constexpr uint32_t kTeamSpins = 1u << 16;
 
-// A colour pass of its own launch takes about 4.4 us on a lattice this small
-// (sc 24^3 .. 64^3: 8.7 to 9.3 us per sweep, 14.5 to 15.4 measured).
+// Plans whose colour phases look longer than this are not considered.
 constexpr double kTeamPhaseUs = 4.5;
 // Box sites of a handle: beyond, a pass launch is no longer mostly overhead.
 constexpr uint64_t kTeamSites = 400000;
@@ -31,8 +30,52 @@ struct TeamPlan {
     uint64_t words = 0;
     uint32_t lds = 0;
     int threads = 0;
-    double phase_us = 0.0; // expected time of a colour phase
+    uint32_t most = 1, polls = 1, members = 1; // sites of a colour per workgroup, rounds
+                                               // of polled words, largest team
+    double phase_us = 0.0; // bound on the time of a colour phase
     bool teams = false;    // some replica has more than one workgroup
+};
+
+// What n sweeps cost, in us, by teams and without them: the figures behind
+// team_from.  Fitted to 145 lattices and batches (sc, bcc, fcc, both precisions,
+// 4 k to 260 k sites), 1 to 20 sweeps a call; where the two come close the plain
+// kernels are taken.  Per call (launch, filling and writing back the planes) a
+// team costs about 9 us and more with its workgroups, two or four pass launches
+// 3; per colour a team's exchange and updates cost 1.8 us with a hundred sites
+// per workgroup, 2.2 with 512 and 4 to 5 with twice that, a pass 3.4 to 5.
+// Unmeasured, us per call, teams / plain: sc 40^3 one sweep 16.4 / 11.4, 20
+// sweeps 158 / 180; fcc 32^3 20 sweeps 435 / 330; FP64 16^3 one sweep 13.3 / 17.
+struct TeamCost {
+    bool f64, fcc, bcc, tile, lds; // tile: the pass kernel is not a pair or band kernel
+    uint32_t most, polls, threads, grid, members, lds_sites;
+    int nc;
+    double team(uint32_t n, bool measure) const
+    {
+        const double low = std::min(most, 512u), high = most - low;
+        double phase = f64 ? (fcc ? 2.85 : bcc ? 2.6 : 2.15) + (bcc ? 0.0016 : 0.0018) * low
+                           : (fcc ? 2.45 : bcc ? 2.2 : 1.75) + 0.0008 * low;
+        phase += (f64 ? 0.004 : fcc ? 0.0018 : bcc ? 0.002 : 0.0024) * high;
+        phase += (f64 ? 2.0 : fcc ? 1.65 : bcc ? 1.3 : 0.9) * (polls - 1);
+        if (tile && !fcc && !bcc) phase += f64 ? 0.3 : 0.15; // a sphere's test per site
+        if (measure) phase += fcc ? 0.2 : 0.35;
+        double t = 8.8 + 0.032 * grid + (fcc ? 2.0 : 0.0) + n * nc * phase;
+        // the records: one workgroup adds its team's sums, 8 n of them at a time
+        if (measure) t += 0.8 + 0.16 * members * ((8u * n + threads - 1) / threads);
+        return t;
+    }
+    double plain(uint32_t n, bool measure) const
+    {
+        if (lds) { // per colour by its sites; a measured call's records are copied
+            const double site = f64 ? (fcc ? 0.0033 : bcc ? 0.0026 : 0.0020)
+                                    : (fcc ? 0.0022 : bcc ? 0.0018 : 0.0012);
+            return 8.0 + (measure ? 8.0 : 0.0) + n * (nc * site * lds_sites + (measure ? 1.2 : 0.0));
+        }
+        const bool basis = fcc || bcc;
+        double pass = f64 ? (fcc ? 4.8 : bcc ? 4.4 : 5.1) : (fcc ? 4.1 : bcc ? 3.75 : 4.3);
+        if (tile) pass = basis ? 1.2 * pass : f64 ? 3.9 : 3.3;
+        const double records = fcc ? 5.6 : bcc ? 2.7 : tile ? 3.3 : 4.0;
+        return 2.9 + n * (nc * pass + (measure ? records : 0.0));
+    }
 };
 
 // Deal every replica's planes so that a workgroup holds about `q` sites of a colour.
@@ -77,6 +120,7 @@ TeamPlan plan_teams(const mc_sim *h, uint32_t q)
             P.wgs.push_back(w);
         }
         P.teams |= members > 1;
+        P.members = std::max(P.members, (uint32_t)members);
         if (members > 1) P.words += (uint64_t)slots * nc * nw * psites;
         P.lds = std::max<uint32_t>(
             P.lds, (uint32_t)std::min<uint64_t>(0xFFFFFFFFu, team_lds_bytes(h->kind, psites, nz, esz)));
@@ -84,10 +128,11 @@ TeamPlan plan_teams(const mc_sim *h, uint32_t q)
         plane_most = std::max(plane_most, psites);
     }
     P.threads = (int)std::min<uint32_t>(TEAM_THREADS, (most + 63u) / 64u * 64u);
-    // microseconds of a colour phase, fitted to sc 16^3 .. 48^3, 17 x 24^3 and
-    // 50 x 37 x 23: the exchange, then rounds of updates and of polled words
+    // the exchange, then rounds of updates and of polled words
     const uint32_t rounds = (most + (uint32_t)P.threads - 1) / (uint32_t)P.threads;
     const uint32_t polls = (plane_most + (uint32_t)P.threads - 1) / (uint32_t)P.threads;
+    P.most = most;
+    P.polls = polls;
     P.phase_us = 1.0 + (h->prec == MC_F64 ? 1.5 : 0.65) * rounds +
                  (h->prec == MC_F64 ? 0.8 : 0.55) * polls;
     return P;
@@ -182,6 +227,27 @@ void team_init(mc_sim *h)
         found = P.wgs.size() * share <= (size_t)cus * (size_t)std::max(0, per_cu);
     }
     if (!found) return;
+    {
+        TeamCost c;
+        c.f64 = f64;
+        c.fcc = h->kind == MC_FCC;
+        c.bcc = h->kind == MC_BCC;
+        c.tile = h->pass_tile.kernel == KERNEL_TILE || h->pass_tile.kernel == KERNEL_BSTRIP;
+        c.lds = h->default_tile.kernel == KERNEL_LDS;
+        c.most = P.most;
+        c.polls = P.polls;
+        c.threads = (uint32_t)P.threads;
+        c.grid = (uint32_t)P.wgs.size();
+        c.members = P.members;
+        c.lds_sites = most;
+        c.nc = h->n_colours;
+        for (int m = 0; m < 2; ++m) {
+            h->team_from[m] = kTeamNever;
+            for (uint32_t n = kTeamChunk; n > 0 && c.team(n, m) < c.plain(n, m); --n)
+                h->team_from[m] = n;
+        }
+        if (h->team_from[0] == kTeamNever && h->team_from[1] == kTeamNever) return;
+    }
     uint64_t o = 0;
     const uint64_t n_state = 4 + 3 * (uint64_t)h->n_reps;
     h->team_off_wgs = (o = align_up(sizeof(uint32_t) * n_state, 256));
@@ -247,6 +313,11 @@ void team_release(mc_sim *h)
     h->team_on = false;
 }
 
+bool team_takes(const mc_sim *h, uint32_t n, bool measure)
+{
+    return h->team_on && n >= h->team_from[measure ? 1 : 0];
+}
+
 mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, TeamHost host)
 {
     TeamLaunch L;
@@ -283,7 +354,7 @@ mc_status enqueue_team(mc_sim *h, uint32_t n, bool measure, uint32_t slot0, Team
 } // namespace mcabi
 
 extern "C" mc_status mc_get_team(mc_sim *h, int32_t replica, int32_t *workgroups, int32_t *planes,
-                                 int32_t *last_planes, uint64_t *redone)
+                                 int32_t *last_planes, uint32_t from_sweeps[2], uint64_t *redone)
 {
     if (!alive(h)) return fail(MC_E_STATE, "invalid or destroyed handle");
     if (replica < 0 || replica >= h->n_reps)
@@ -298,6 +369,8 @@ extern "C" mc_status mc_get_team(mc_sim *h, int32_t replica, int32_t *workgroups
     if (workgroups) *workgroups = n;
     if (planes) *planes = first;
     if (last_planes) *last_planes = last;
+    if (from_sweeps)
+        for (int m = 0; m < 2; ++m) from_sweeps[m] = h->team_on ? h->team_from[m] : kTeamNever;
     if (!redone) return MC_OK;
     *redone = 0;
     if (!h->team_on) return MC_OK;

@@ -112,6 +112,7 @@ _SIGNATURES = {
                                        ctypes.c_double, ctypes.POINTER(Stats)]),
     "mc_get_team": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32),
                                    ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32),
+                                   ctypes.POINTER(ctypes.c_uint32),
                                    ctypes.POINTER(ctypes.c_uint64)]),
     "mc_set_watchdog": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_uint32]),
     "mc_set_persistent_mode": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int]),
@@ -406,13 +407,16 @@ class Simulation:
 
     def team(self, r: int = 0) -> dict:
         """``mc_get_team``: workgroups of replica r's team (0: its sweeps do not
-        run by teams), planes of the first and the last of them, and the
-        handle's teams' launches done again after a wait gave up."""
+        run by teams), planes of the first and the last of them, the sweeps per
+        call from which the teams run them (unmeasured, measured; 2**32 - 1:
+        never), and the handle's teams' launches done again after a wait gave
+        up."""
         v, n = [ctypes.c_int32() for _ in range(3)], ctypes.c_uint64()
-        _check("mc_get_team", LIB.mc_get_team(self.handle, int(r), *[ctypes.byref(x) for x in v],
+        f = (ctypes.c_uint32 * 2)()
+        _check("mc_get_team", LIB.mc_get_team(self.handle, int(r), *[ctypes.byref(x) for x in v], f,
                                               ctypes.byref(n)))
         return {"workgroups": v[0].value, "planes": v[1].value, "last_planes": v[2].value,
-                "redone": n.value}
+                "from": (f[0], f[1]), "redone": n.value}
 
     def set_watchdog(self, spins: int):
         _check("mc_set_watchdog", LIB.mc_set_watchdog(self.handle, int(spins)))

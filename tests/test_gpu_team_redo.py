@@ -23,18 +23,29 @@ def M():
 def test_given_up_sweeps_are_bitwise(M, name):
     a, b = _pair(M, name)
     teams = sum(a.team(r)["workgroups"] > 1 for r in range(a.n_reps))
-    assert teams > 0 and a.team()["redone"] == 0
+    plain, measured = a.team()["from"]
+    if teams == 0:
+        pytest.skip("never swept by teams")
+    assert a.team()["redone"] == 0
+    # as many sweeps as the teams take, and more (calls that they never take: one)
+    calls = [(min(n + k, 64) if n <= 64 else 1, m) for k in (0, 3)
+             for m, n in ((True, measured), (False, plain))]
+    by_teams = 2 * (measured <= 64) + 2 * (plain <= 64)
+    assert by_teams > 0
     launches = 0
     for spins in (0, 1 << 24, 0):
         a.set_watchdog(spins)
-        for n, measure in ((1, True), (3, False), (2, True), (1, False)):
+        for n, measure in calls:
             a.sweep(n, measure=measure)
             b.sweep(n, measure=measure)
         a.synchronize_checked()
-        launches += 0 if spins else 4
+        launches += 0 if spins else by_teams
         assert a.team()["redone"] == launches * teams
         _same_spins(a, b)
         _same_obs(a.observables(), b.observables())
+        for s in (a, b):
+            s.sweep(1, measure=True)
+        launches += (spins == 0) * (measured == 1)
     assert [o["n_sites"] for o in a.measure_state()] == a.n_occ
 
 

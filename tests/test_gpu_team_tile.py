@@ -44,7 +44,7 @@ def test_default_tile_brings_the_teams_back(M, name):
     a.set_tile(tx, ty, zc, kernel=k)
     assert a.team() == team and a.get_tile()[:4] == (k, tx, ty, zc)
     for s in (a, b):
-        s.sweep(3, measure=True)
+        s.sweep(9, measure=True)
     _same_spins(a, b)
     _same_obs(a.observables(), b.observables())
 
@@ -60,8 +60,8 @@ def test_timed_sweeps_run_the_teams(M, name):
         b.sweep(70, measure=measure)
     a.set_watchdog(0)
     before = a.team()["redone"]
-    a.sweep_timed(2)
-    b.sweep(2)
+    a.sweep_timed(9)
+    b.sweep(9)
     assert a.team()["redone"] == before + a.n_reps
     _same_spins(a, b)
     _same_obs(a.observables(), b.observables())

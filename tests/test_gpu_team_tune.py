@@ -60,7 +60,7 @@ def test_cache_keeps_the_teams_choice(M, tmp_path, name, tune_launch):
     other = hit(" ".join([fields[0], "0", "8", "8", "2", "0.01", "0", "1"]))
     assert other.get_tile()[:4] == (0, 8, 8, 2) and other.team()["workgroups"] == 0
     for s in (with_teams, without, old, again, other):
-        s.sweep(3, measure=True)
+        s.sweep(12, measure=True)
         _same_spins(s, with_teams)
         _same_obs(s.observables(), with_teams.observables())
 

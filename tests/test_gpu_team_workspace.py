@@ -48,6 +48,6 @@ def test_team_after_autotune_of_an_lds_default(M, name, spare):
         _same_obs(a.measure_state(), b.measure_state())
         for s in (a, b):
             s.block_steps(8, 0, 2)
-            s.sweep(3, measure=True)
+            s.sweep(12, measure=True)
         _same_spins(a, b)
         _same_obs(a.observables(), b.observables())
