@@ -137,7 +137,11 @@ uint64_t xy_tiles(const mc_replica_desc &d, const Tile &t)
 //  * a lattice whose workgroups all fit the GPU at once (about 1024 FP32, 512
 //    FP64) with at most 8 planes each does best as that one round: 32 x 64^3
 //    zc 1 62.8 / 86.1, zc 8 60.9 / 66.7; FP64 128^3 zc 1 42.4 / 56.6, zc 4
-//    35.9 / 43.0; bcc 128^3 zc 1 35.1 / 43.5, zc 4 30.4 / 37.6;
+//    35.9 / 43.0; bcc 128^3 zc 1 35.1 / 43.5, zc 4 30.4 / 37.6 -- but from 1.4
+//    rounds of workgroups of one plane on: 16 x 40^3 (1.25) zc 1 15.4 / 21.0, zc 2
+//    16.3 / 22.1, FP64 80^3 (1.1) zc 1 18.2 / 27.2, zc 2 20.0 / 26.6, 112^3 (1.4)
+//    18.6 / 26.9, 17.8 / 24.1; and in FP32 fcc with two planes at most: 160^3 (3.9)
+//    zc 1 153 / 170, zc 2 152 / 163, zc 4 156 / 167;
 //  * a larger one with about 6000 workgroups (FP64 3500): 302 x 251 x 210 zc 2
 //    104 / 120, zc 3 104 / 113, zc 5 115 / 119; 464^3 zc 14 803 / 805, zc 8
 //    766 / 780; FP64 464^3 zc 5 1576 / 1611, zc 16 1570 / 1582, zc 24 1576 / 1589;
@@ -170,7 +174,14 @@ int z_chunk(const mc_replica_desc *reps, int n, const Tile &t, size_t esz)
                                      : reps[0].kind == MC_FCC ? 2048 : 1024;
         const uint64_t many = f64 ? 3500 : 6000;
         zc = (p + round - 1) / round;
-        if (zc > 8) zc = (p + many / 2) / many;
+        if (zc > 8) {
+            zc = (p + many / 2) / many;
+        } else if (!flat) {
+            // a round that is little more than half full loses to one and a bit
+            if (5 * p < 7 * round) zc = 1;
+            // fcc FP32 gains nothing from taller chunks
+            else if (!f64 && reps[0].kind == MC_FCC && !sphere) zc = std::min<uint64_t>(zc, 2);
+        }
         // a sphere leaves about half of its box's rows empty or short (fcc
         // 128^3, R = 60: zc 4 68.7 / 77.4, zc 2 65.8 / 75.2)
         if (sphere) zc = (zc + 1) / 2;
