@@ -47,14 +47,15 @@ struct TeamPlan {
 // sweeps 158 / 180; fcc 32^3 20 sweeps 435 / 330; FP64 16^3 one sweep 13.3 / 17.
 struct TeamCost {
     bool f64, fcc, bcc, tile, lds; // tile: the pass kernel is not a pair or band kernel
-    uint32_t most, polls, threads, grid, members, lds_sites;
+    bool ragged;                   // rows that are no multiple of 64 bytes
+    uint32_t most, polls, threads, grid, members, lds_sites, items;
     int nc;
     double team(uint32_t n, bool measure) const
     {
         const double low = std::min(most, 512u), high = most - low;
         double phase = f64 ? (fcc ? 2.85 : bcc ? 2.6 : 2.15) + (bcc ? 0.0016 : 0.0018) * low
                            : (fcc ? 2.45 : bcc ? 2.2 : 1.75) + 0.0008 * low;
-        phase += (f64 ? 0.004 : fcc ? 0.0018 : bcc ? 0.002 : 0.0024) * high;
+        phase += (f64 ? 0.004 : fcc || polls > 1 ? 0.0018 : bcc ? 0.002 : 0.0024) * high;
         phase += (f64 ? 2.0 : fcc ? 1.65 : bcc ? 1.3 : 0.9) * (polls - 1);
         if (tile && !fcc && !bcc) phase += f64 ? 0.3 : 0.15; // a sphere's test per site
         if (measure) phase += fcc ? 0.2 : 0.35;
@@ -71,9 +72,12 @@ struct TeamCost {
             return 8.0 + (measure ? 8.0 : 0.0) + n * (nc * site * lds_sites + (measure ? 1.2 : 0.0));
         }
         const bool basis = fcc || bcc;
-        double pass = f64 ? (fcc ? 4.8 : bcc ? 4.4 : 5.1) : (fcc ? 4.1 : bcc ? 3.75 : 4.3);
-        if (tile) pass = basis ? 1.2 * pass : f64 ? 3.9 : 3.3;
-        const double records = fcc ? 5.6 : bcc ? 2.7 : tile ? 3.3 : 4.0;
+        double pass = f64 ? (fcc ? 4.8 : bcc ? 4.4 : 5.1)
+                          : (fcc ? 4.1 : bcc ? 3.75 : ragged ? 4.5 : 4.3);
+        if (tile) pass = basis ? 1.25 * pass : f64 ? 3.9 : 3.3;
+        // the reduction's launch and a share per workgroup of the passes
+        const double records = (fcc ? 5.6 : bcc ? 4.2 : 4.0) +
+                               (tile ? 0.005 : 0.0025) * items;
         return 2.9 + n * (nc * pass + (measure ? records : 0.0));
     }
 };
@@ -240,6 +244,9 @@ void team_init(mc_sim *h)
         c.grid = (uint32_t)P.wgs.size();
         c.members = P.members;
         c.lds_sites = most;
+        c.ragged = false;
+        for (const RepDev &R : h->reps) c.ragged |= R.Lxh % 16 != 0;
+        c.items = (uint32_t)h->work.size();
         c.nc = h->n_colours;
         for (int m = 0; m < 2; ++m) {
             h->team_from[m] = kTeamNever;
