@@ -256,8 +256,10 @@ Tile default_tile(const mc_replica_desc *reps, int n, size_t esz)
         // other bases' rows in registers), and so does bcc in FP64 (200^3 290
         // -> 250 us) or from the 256 MB cache (128^3 31.3 / 38.2 -> 30.4 / 37.6
         // us); beyond, two rows re-read less (368^3 743 / 752 -> 733 / 750 us).
-        // One wave per workgroup where a sphere leaves rows to drop (fcc 128^3,
-        // R = 60: 66.5 / 82.5 -> 65.8 / 75.2).
+        // One wave per workgroup where a sphere leaves rows to drop (48^3 to 200^3,
+        // R 22 to 100: FP32 within 3 % of 256 lanes either way, fcc 96^3 37.2 / 48.6
+        // -> 35.1 / 45.9; FP64 2 to 10 % faster, bcc 200^3, R = 95, 198 / 214 ->
+        // 181 / 198).
         t.kernel = KERNEL_BPAIR;
         t.tx = cut ? 64 : 256;
         t.ty = reps[0].kind == MC_FCC || esz == sizeof(double) || bytes <= 256000000ull ? 1 : 2;
